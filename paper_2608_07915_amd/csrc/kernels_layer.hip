@@ -13,17 +13,16 @@
 //                         per token and kept group fp16 zero-point and scale, codes,
 //                         packing; one workgroup per (256 tokens, kept group, stream);
 //   layer_decode_kernel   x_hat = sum_G (s_tG q_tG + z_tG 1) V_G^T + m V^T: codes
-//                         unpacked once per workgroup into LDS as bf16, the basis
-//                         columns of the group as three bf16 parts, the group's
-//                         per-token scale applied after its product; one workgroup per
-//                         (128 tokens, 128 channels, stream).
+//                         unpacked in registers, the basis columns of a group as two
+//                         fp16 parts in LDS, the group's per-token scale applied after
+//                         its product; persistent workgroups of 128 channels.
+#include "attn_common.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "layer.hpp"
+#include "layer_codes.hpp"
 
 namespace spectra_dev {
-
-constexpr int LG = 64;  // latent group size of the per-layer geometry
 
 // Kept group `slot` of a per-layer stream (widths bits_s[0..ng)): group index, width
 // and first payload word; also the number of kept groups and the record words used.
@@ -324,188 +323,316 @@ __global__ __launch_bounds__(512, 4) void layer_encode_kernel(LayerEncodeArgs a)
 // ---------------------------------------------------------------------------
 // Decode (Mode A)
 // ---------------------------------------------------------------------------
-// One workgroup: LD_CH = 64 output channels x LD_NT = 2 tiles of 128 tokens. The
-// group's basis operands and the mean term m V^T are built once per workgroup and
-// serve both tiles (the L2 reads of basis rows per token are what bound this kernel).
-// Registers are capped at 128 per lane so that two workgroups (four wavefronts per
-// SIMD) share a CU and hide each other's load latency; per-piece shift amounts are
-// scalar and record offsets are recomputed per slot, so almost nothing spills.
-constexpr int LD_TOK = 128;       // tokens per tile
-constexpr int LD_NT = 2;          // tiles per workgroup
-constexpr int LD_CH = 64;         // output channels per workgroup
-constexpr int LD_P = LG + 8;      // bf16 per LDS row (144 bytes)
-constexpr int LD_R = 2 * LD_NT;   // staged (token, 8-code) pieces per thread
+// One workgroup: 128 output channels, walking ranges of 256 tokens (wavefront w: 32 tokens x
+// all 128 channels). What depends on the channels alone is computed once per workgroup:
+// m V^T, the sums of the basis entries of each kept group and the power of two that brings
+// a group's largest entry into [2^8, 2^9). Then, per kept group of a range, the 128 x 64
+// basis block goes to LDS as two fp16 parts (two buffers: the next block is split while
+// this one is multiplied) and each lane turns its token's payload words into operands in
+// registers:
+//   out[ch][t] += s_t (sum_j V[ch][j] q'_tj), q' the codes centered on 0.
+// Two fp16 parts of the scaled entries keep 22 bits and take two products where three bf16
+// parts took three; centering the codes halves the magnitude of the fp32 sums, so the error
+// against 64 bits went down (2.9e-7 -> 2.3e-7). The zero-point terms (z_t + 2^(b-1) s_t)
+// sum_j V[ch][j] of all groups are one product over the slots per range (three bf16 parts
+// each side), and m V^T is added last.
+// A 131k-token 1024-wide layer at 8x: 1830 -> 495 us. Matrix cores busy 42%, vector ALU
+// 40%, the rest is the store bursts at a range's end (90 us of it with the stores removed)
+// and waiting inside a step. What was tried and is slower: a workgroup per range (720 us:
+// its prologue and epilogue overlap nothing), 64 tokens x 64 channels per wavefront (560
+// us, every code unpacked twice), 64 x 128 (490 to 520 us, spills), four wavefronts
+// with four times the registers (770 us).
+constexpr int LD_CH = 128;     // channels per workgroup
+constexpr int LD_NW = 8;       // wavefronts per workgroup
+constexpr int LD_TOK = 32 * LD_NW;  // tokens per range
+constexpr int LD_P = LG + 8;   // fp16 per LDS row (144 bytes: 16 rows on distinct banks)
+constexpr int LD_YP = 24;      // bf16 per row of the group sums (16 slots + pad)
+constexpr int LD_ZP = 20;      // floats per row of the zero points (16 slots + pad)
 
-__global__ __launch_bounds__(512, 4) void layer_decode_kernel(LayerDecodeArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t vsl[3][LD_CH][LD_P];          // basis columns of the group, [channel][coef]
-  __shared__ __attribute__((aligned(16))) uint16_t cod[LD_NT][LD_TOK][LD_P];     // codes, [tile][token][coef]
-  __shared__ __attribute__((aligned(16))) float sl[LD_NT][LD_TOK], zl[LD_NT][LD_TOK], vsum[LD_CH], bias[LD_CH];
+// The exponent e with v in [2^(e-1), 2^e), limited so that 2^(9 - e) and its inverse are normal.
+__device__ __forceinline__ int scale_exponent(float v) {
+  int e = 0;
+  if (v > 0.0f && v < __builtin_inff()) (void)__builtin_frexpf(v, &e);
+  return e < -100 ? -100 : (e > 100 ? 100 : e);
+}
+__device__ __forceinline__ void split_row3(const float (&x)[8], bf16x8 (&p)[3]) {
+  uint32_t p0[8], p1[8], p2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) split3(x[i], p0[i], p1[i], p2[i]);
+  p[0] = as_bf16x8(u32x4{pack2(p0[0], p0[1]), pack2(p0[2], p0[3]), pack2(p0[4], p0[5]), pack2(p0[6], p0[7])});
+  p[1] = as_bf16x8(u32x4{pack2(p1[0], p1[1]), pack2(p1[2], p1[3]), pack2(p1[4], p1[5]), pack2(p1[6], p1[7])});
+  p[2] = as_bf16x8(u32x4{pack2(p2[0], p2[1]), pack2(p2[2], p2[3]), pack2(p2[4], p2[5]), pack2(p2[6], p2[7])});
+}
+
+template <bool SCALED>
+__global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecodeArgs a) {
+  constexpr int NT = 64 * LD_NW;
+  static_assert(NT == 4 * LD_CH, "a thread stages a quarter of a channel's 64 coefficients");
+  __shared__ __attribute__((aligned(16))) uint16_t vl[2][2][LD_CH][LD_P];  // [buffer][part][channel][place]
+  __shared__ __attribute__((aligned(16))) uint16_t yl[3][LD_CH][LD_YP];    // [part][channel][slot]: group sums
+  __shared__ __attribute__((aligned(16))) float zl[LD_TOK][LD_ZP];         // [token][slot]: centered zero points
+  __shared__ __attribute__((aligned(16))) float bias[LD_CH];
+  __shared__ __attribute__((aligned(16))) float mean[1024];
+  __shared__ float vmax[16][LD_NW];
+  __shared__ int vexp[16];
+  __shared__ LayerTable tab;
   const int s = blockIdx.z;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, h = lane >> 5;
-  const int d = a.d, ng = d / LG;
-  int range, cblk;
-  xcd_major_block((int)((a.n + LD_TOK * LD_NT - 1) / (LD_TOK * LD_NT)), d / LD_CH, range, cblk);
-  if (range < 0) return;
-  const int ch0 = cblk * LD_CH;
-  const int64_t tok0 = (int64_t)range * (LD_TOK * LD_NT);
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int d = a.d, ng = d / LG, nb = d / LD_CH;
+  // channel block fastest: with eight blocks each XCD keeps one 128-row basis slice in its
+  // L2 and streams the records, which are several times smaller than the rows they rebuild
+  const int ch0 = (int)(blockIdx.x % (unsigned)nb) * LD_CH;
+  const int64_t n_ranges = (a.n + LD_TOK - 1) / LD_TOK;
+  const int64_t r_step = gridDim.x / (unsigned)nb;
   const int64_t sbase = (int64_t)s * a.t_cap * a.W;
   const float* Vs = a.basis + (int64_t)s * d * d;
-  const uint8_t* bits_s = a.bits + (int64_t)s * ng;
-  const LayerSlot k0 = layer_slot(bits_s, ng, 0);
-  if (!k0.ok || k0.used > a.W) return;  // width table inconsistent with the record: write nothing
-  const int n_kept = k0.n_kept;
+  if (tid == 0) layer_table(a.bits + (int64_t)s * ng, ng, tab);
+  for (int i = tid; i < d; i += NT) mean[i] = a.mean[(int64_t)s * d + i];
+  for (int i = tid; i < 3 * LD_CH * LD_YP / 2; i += NT) reinterpret_cast<uint32_t*>(yl)[i] = 0u;  // slots past the kept ones
+  for (int i = tid; i < LD_TOK * LD_ZP; i += NT) reinterpret_cast<float*>(zl)[i] = 0.0f;
+  __syncthreads();
+  if (!tab.ok || tab.used > a.W) return;  // width table inconsistent with the record: write nothing
+  const int n_kept = __builtin_amdgcn_readfirstlane(tab.n_kept);
 
-  // per-thread shares of a slot's staging: basis row (channel tid >> 3) coefficients
-  // 8 (tid & 7) .. + 7; piece r: token u_r = (tid + 512 r) & 127 of tile (tid + 512 r) >> 10,
-  // coefficients 8 k8_r .. + 7 with k8_r = ((tid + 512 r) >> 7) & 7 (uniform in a wavefront)
-  const int vc = tid >> 3, vq = tid & 7;
-  // ((tid + 512 r) >> 7) & 7 = (kq + 4 r) & 7 with kq = tid >> 7, uniform in a wavefront:
-  // held in a scalar register, so the shift amounts derived from it are scalar too
-  const int kq = __builtin_amdgcn_readfirstlane(tid >> 7);
-  float vpre[8];
-  uint32_t wpre[LD_R][3], mpre[LD_R];
-  auto prefetch = [&](const LayerSlot& ks, int slot) {
-    const float* vr = Vs + (int64_t)(ch0 + vc) * d + LG * ks.grp + 8 * vq;
+  // staging share: channel row tid >> 2, group coefficients c0 .. c0 + 7 and c0 + 16 ..
+  // c0 + 23, which are 16 consecutive places of the operand row
+  const int row = tid >> 2, sub = tid & 3, c0 = 32 * (sub >> 1) + 8 * (sub & 1);
+  float v[16];
+  auto load_v = [&](int g, float (&x)[16]) {
+    const float* src = Vs + (int64_t)(ch0 + row) * d + LG * g + c0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) vpre[i] = vr[i];
-    // record word 0 of the thread's token in each tile, recomputed per call rather than
-    // held in registers across the slot loop
-    int u = tid & (LD_TOK - 1);
-    asm volatile("" : "+v"(u));
-    int64_t tb[LD_NT];
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<f32x4*>(&x[4 * q]) = *reinterpret_cast<const f32x4*>(src + 16 * (q >> 1) + 4 * (q & 1));
+  };
+  // square-root split: c_hat_j / f_j folded into the basis columns
+  auto scale_v = [&](int g, float (&x)[16]) {
+    if constexpr (SCALED) {
+      const float* f = a.lscale + (int64_t)s * d + LG * g + c0;
 #pragma unroll
-    for (int t2 = 0; t2 < LD_NT; ++t2) {
-      const int64_t i = tok0 + (int64_t)t2 * LD_TOK + u;
-      tb[t2] = rec_word(sbase, a.t0 + (i < a.n ? i : a.n - 1), a.W, 0);
+      for (int i = 0; i < 16; ++i) x[i] *= 1.0f / f[16 * (i >> 3) + (i & 7)];
+    }
+  };
+  {
+    float bsum = 0.0f, x[2][16];
+    load_v(__builtin_amdgcn_readfirstlane(tab.grp[0]), x[0]);
+    for (int k0 = 0; k0 < ng; k0 += 2) {  // d is a multiple of 128: an even number of groups
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int k = k0 + u, g = __builtin_amdgcn_readfirstlane(tab.grp[k]);
+        load_v(__builtin_amdgcn_readfirstlane(tab.grp[k + 1 < ng ? k + 1 : k]), x[u ^ 1]);
+        float(&xc)[16] = x[u];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) bsum = __builtin_fmaf(mean[LG * g + c0 + 16 * (i >> 3) + (i & 7)], xc[i], bsum);
+        if (k < n_kept) {
+          scale_v(g, xc);
+          float m = 0.0f, sum = 0.0f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            sum += xc[i];
+            m = __builtin_fmaxf(m, __builtin_fabsf(xc[i]));
+          }
+          sum += __shfl_xor(sum, 1);
+          sum += __shfl_xor(sum, 2);
+          uint32_t p0, p1, p2;
+          split3(sum, p0, p1, p2);
+          if (sub < 3) yl[sub][row][k] = (uint16_t)(sub == 0 ? p0 : sub == 1 ? p1 : p2);
+          m = wave_max_all(m);
+          if (lane == 0) vmax[k][wave] = m;
+        }
+      }
+    }
+    bsum += __shfl_xor(bsum, 1);
+    bsum += __shfl_xor(bsum, 2);
+    if (sub == 0) bias[row] = bsum;
+  }
+  __syncthreads();
+  if (tid < n_kept) {
+    float m = vmax[tid][0];
+#pragma unroll
+    for (int w = 1; w < LD_NW; ++w) m = __builtin_fmaxf(m, vmax[tid][w]);
+    vexp[tid] = 9 - scale_exponent(m);
+  }
+  __syncthreads();
+
+  // slot tables, one slot per lane: read by v_readlane with a scalar slot, no memory access
+  const int tl = lane & 15;
+  const int slot_grp = tab.grp[tl < ng ? tl : 0], slot_b = tl < n_kept ? tab.b[tl] : 0, slot_pay = tl < n_kept ? tab.pay[tl] : 0;
+  const int slot_exp = tl < n_kept ? vexp[tl] : 0;
+  auto of_slot = [](int table, int slot) { return __builtin_amdgcn_readlane(table, slot); };
+
+  // the group in v to buffer buf as two fp16 parts
+  auto split_v = [&](int slot, int buf) {
+    const float sc = __builtin_ldexpf(1.0f, of_slot(slot_exp, slot));
+    uint32_t hi[8], lo[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // coefficients c0 + i and c0 + 16 + i are neighbours in K
+      const f32x2 x = f32x2{v[i] * sc, v[8 + i] * sc};
+      const f16x2 xh = __builtin_convertvector(x, f16x2);
+      const f16x2 xl = __builtin_convertvector(f32x2{x[0] - (float)xh[0], x[1] - (float)xh[1]}, f16x2);
+      hi[i] = __builtin_bit_cast(uint32_t, xh);
+      lo[i] = __builtin_bit_cast(uint32_t, xl);
     }
 #pragma unroll
-    for (int r = 0; r < LD_R; ++r) {
-      const int k8 = (kq + 4 * r) & 7, t2 = r >> 1;
-      const int P = 8 * k8 * ks.b, w0 = P >> 5, wl = (P + 8 * ks.b - 1) >> 5;  // payload words extract8 reads
-#pragma unroll
-      for (int i = 0; i < 3; ++i) wpre[r][i] = (w0 + i <= wl) ? a.packed[tb[t2] + (int64_t)(ks.pay + w0 + i) * TILE] : 0u;
-      mpre[r] = a.packed[tb[t2] + (int64_t)slot * TILE];
+    for (int q = 0; q < 2; ++q) {
+      *reinterpret_cast<u32x4*>(&vl[buf][0][row][16 * sub + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
+      *reinterpret_cast<u32x4*>(&vl[buf][1][row][16 * sub + 8 * q]) = u32x4{lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]};
     }
   };
 
-  // bias = m V^T over all d coefficients: wavefront w takes channels 8w .. 8w + 7,
-  // each row read by the whole wavefront (16 values per lane), then a wavefront sum
-  {
-    const float* mr = a.mean + (int64_t)s * d;
-    float mv[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) mv[i] = (64 * i + lane < d) ? mr[64 * i + lane] : 0.0f;
-    float part[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const float* vr = Vs + (int64_t)(ch0 + 8 * wave + c) * d;
-      float acc = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (64 * i + lane < d) acc = __builtin_fmaf(mv[i], vr[64 * i + lane], acc);
-      part[c] = acc;
+  // this lane's token of a range is row tw + col
+  const int tw = 32 * wave;
+  const uint32_t* rec = nullptr;
+  uint32_t words[8], meta = 0u;
+  int64_t range = blockIdx.x / (unsigned)nb;
+  // record words of the next slot to come (all slots of a range, then the next range;
+  // tokens past the last one read the last one)
+  int w_slot = 0;
+  int64_t w_range = range;
+  auto next_words = [&]() {
+    if (w_slot == 0) {
+      const int64_t i = w_range * LD_TOK + tw + col;
+      rec = a.packed + rec_word(sbase, a.t0 + (i < a.n ? i : a.n - 1), a.W, 0);
+      w_range += r_step;
     }
+    const int b = of_slot(slot_b, w_slot), pay = of_slot(slot_pay, w_slot);
+    const uint32_t* src = rec + (pay + h * b) * TILE;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      float v = part[c];
+    for (int i = 0; i < 8; ++i)
+      if (i < b) words[i] = src[i * TILE];
+    meta = rec[w_slot * TILE];
+    w_slot = w_slot + 1 < n_kept ? w_slot + 1 : 0;
+  };
+  uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
+  asm volatile("" : "+v"(magic));
+  // operands, scale and centered zero point of the slot whose words are held
+  f16x8 cod[4];
+  float st = 0.0f, zc = 0.0f;
+  int u_slot = 0;
+  auto unpack = [&]() {
+    const int bw = of_slot(slot_b, u_slot);
+    with_bits(bw, [&](auto bc) {
+      constexpr int B = decltype(bc)::value;
+      uint32_t Z[8];
+      join_halves<B>(words, Z);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (lane == c) bias[8 * wave + c] = v;
+      for (int k = 0; k < 4; ++k) cod[k] = codes_f16<B>(Z, k, magic);
+    });
+    const float sv = h2f(meta);
+    st = sv * __builtin_ldexpf(1.0f, -of_slot(slot_exp, u_slot));
+    zc = __builtin_fmaf(sv, (float)(1 << (bw - 1)), h2f(meta >> 16));
+    u_slot = u_slot + 1 < n_kept ? u_slot + 1 : 0;
+  };
+  f32x16 out[4];  // 32-channel blocks
+  auto multiply = [&](int slot, int buf) {
+    zl[tw + col][slot] = zc;
+    // operands are read two K steps ahead and a channel block's sums are added while the
+    // next block's products run
+    constexpr int AHEAD = 2;
+    f16x8 ah[AHEAD + 1], al[AHEAD + 1];
+    f32x16 g[2];
+    auto read_op = [&](int t) {
+      const uint16_t* src = &vl[buf][0][32 * (t >> 2) + col][32 * h + 8 * (t & 3)];
+      ah[t % (AHEAD + 1)] = *reinterpret_cast<const f16x8*>(src);
+      al[t % (AHEAD + 1)] = *reinterpret_cast<const f16x8*>(src + LD_CH * LD_P);
+    };
+    auto add_block = [&](int cb) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) out[cb][i] = __builtin_fmaf(st, g[cb & 1][i], out[cb][i]);
+    };
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t) read_op(t);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int cb = t >> 2, k = t & 3;
+      if (t + AHEAD < 16) read_op(t + AHEAD);
+      if (k == 0) g[cb & 1] = f32x16{};
+      g[cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[t % (AHEAD + 1)], cod[k], g[cb & 1], 0, 0, 0);
+      g[cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[t % (AHEAD + 1)], cod[k], g[cb & 1], 0, 0, 0);
+      if (k == 3 && cb > 0) add_block(cb - 1);
     }
-  }
+    add_block(3);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * AHEAD, 0);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      if (t + AHEAD < 16) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      if (t >= 5) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+    }
+    // the sums stay here (not sunk past the next blocks with all products alive)
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) asm volatile("" : "+v"(out[cb]));
+  };
 
-  // wavefront -> channel block cb (32 channels), tile tl, token blocks 2 tp, 2 tp + 1
-  // (32 tokens each) of that tile
-  const int cb = wave & 1, tl = (wave >> 1) >> 1, tp = (wave >> 1) & 1;
-  f32x16 out[2] = {f32x16{}, f32x16{}};
-  LayerSlot ks = k0;
-  if (n_kept > 0) prefetch(ks, 0);
-  for (int slot = 0; slot < n_kept; ++slot) {
-    // stage the prefetched slot: codes as bf16 and metadata, basis parts and sums
-    int kqs = kq;
-    asm volatile("" : "+s"(kqs));  // shift amounts recomputed per slot (scalar), not hoisted
-#pragma unroll
-    for (int r = 0; r < LD_R; ++r) {
-      const int u = tid & (LD_TOK - 1), k8 = (kqs + 4 * r) & 7, t2 = r >> 1;
-      const int w0 = (8 * k8 * ks.b) >> 5;
-      with_bits(ks.b, [&](auto bc) {
-        constexpr int B = decltype(bc)::value;
-        uint32_t cd[8];
-        extract8<B>([&](int i) { return wpre[r][i - w0]; }, 8 * k8, cd);
-        *reinterpret_cast<u32x4*>(&cod[t2][u][8 * k8]) =
-            u32x4{int_to_bf16_pair(cd[0], cd[1]), int_to_bf16_pair(cd[2], cd[3]), int_to_bf16_pair(cd[4], cd[5]),
-                  int_to_bf16_pair(cd[6], cd[7])};
-      });
-      if (k8 == 0) {
-        sl[t2][u] = h2f(mpre[r]);
-        zl[t2][u] = h2f(mpre[r] >> 16);
-      }
-    }
-    {
-      if (a.lscale) {  // square-root split: c_hat_j / f_j, folded into the basis columns
-        const float* fr = a.lscale + (int64_t)s * d + LG * ks.grp + 8 * vq;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) vpre[i] = vpre[i] * (1.0f / fr[i]);
-      }
-      float sum = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) sum += vpre[i];
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      sum += __shfl_xor(sum, 4);
-      if (vq == 0) vsum[vc] = sum;
-      uint32_t p0[8], p1[8], p2[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) split3(vpre[i], p0[i], p1[i], p2[i]);
-      const int j = 8 * vq;
-      *reinterpret_cast<u32x4*>(&vsl[0][vc][j]) = u32x4{pack2(p0[0], p0[1]), pack2(p0[2], p0[3]), pack2(p0[4], p0[5]), pack2(p0[6], p0[7])};
-      *reinterpret_cast<u32x4*>(&vsl[1][vc][j]) = u32x4{pack2(p1[0], p1[1]), pack2(p1[2], p1[3]), pack2(p1[4], p1[5]), pack2(p1[6], p1[7])};
-      *reinterpret_cast<u32x4*>(&vsl[2][vc][j]) = u32x4{pack2(p2[0], p2[1]), pack2(p2[2], p2[3]), pack2(p2[4], p2[5]), pack2(p2[6], p2[7])};
-    }
-    __syncthreads();
-    if (slot + 1 < n_kept) {
-      ks = layer_slot(bits_s, ng, slot + 1);
-      prefetch(ks, slot + 1);
-    }
-    // D[channel][token] = sum_j V[channel][j] q[token][j] for this group
-    f32x16 g[2] = {f32x16{}, f32x16{}};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const bf16x8 b0 = as_bf16x8(*reinterpret_cast<const u32x4*>(&cod[tl][64 * tp + col][16 * k + 8 * h]));
-      const bf16x8 b1 = as_bf16x8(*reinterpret_cast<const u32x4*>(&cod[tl][64 * tp + 32 + col][16 * k + 8 * h]));
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        const bf16x8 av = as_bf16x8(*reinterpret_cast<const u32x4*>(&vsl[p][32 * cb + col][16 * k + 8 * h]));
-        g[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b0, g[0], 0, 0, 0);
-        g[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b1, g[1], 0, 0, 0);
-      }
-    }
-    // lane (h, col): rows 4h + (i & 3) + 8 (i >> 2) = channels, column col = token
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-      const int u = 64 * tp + 32 * tb + col;
-      const float st = sl[tl][u], zt = zl[tl][u];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 vs4 = *reinterpret_cast<const f32x4*>(&vsum[32 * cb + 4 * h + 8 * q]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[tb][4 * q + j] += st * g[tb][4 * q + j] + zt * vs4[j];
-      }
+  // Half of the wavefronts run the halves of a step in the opposite order (and unpack a
+  // slot ahead), so that some split and unpack while others multiply.
+  const bool ahead = wave >= LD_NW / 2;
+  int buf = 0;
+  if (n_kept > 0 && range < n_ranges) {
+    next_words();
+    const int g0 = of_slot(slot_grp, 0);
+    load_v(g0, v);
+    scale_v(g0, v);
+    split_v(0, 0);
+    const int g1 = of_slot(slot_grp, n_kept > 1 ? 1 : 0);
+    load_v(g1, v);
+    scale_v(g1, v);
+    if (ahead) {
+      unpack();
+      next_words();
     }
     __syncthreads();
   }
-  if (n_kept == 0) __syncthreads();  // bias visible
+  for (; range < n_ranges; range += r_step) {
 #pragma unroll
-  for (int tb = 0; tb < 2; ++tb) {
-    const int64_t i = tok0 + (int64_t)tl * LD_TOK + 64 * tp + 32 * tb + col;
-    if (i < a.n) {
-      float* o = a.out + ((int64_t)s * a.n + i) * d + ch0 + 32 * cb + 4 * h;
+    for (int cb = 0; cb < 4; ++cb) out[cb] = f32x16{};
+    // slot k of a range is multiplied from buffer buf while slot k + 1 is split into the
+    // other and the basis block of slot k + 2 is loaded (modulo the kept slots: the next
+    // range uses the same blocks); past the last range the prefetches repeat its words
+    for (int slot = 0; slot < n_kept; ++slot) {
+      const int s1 = slot + 1 < n_kept ? slot + 1 : 0, s2 = s1 + 1 < n_kept ? s1 + 1 : 0;
+      if (ahead) multiply(slot, buf);
+      split_v(s1, buf ^ 1);
+      const int g2 = of_slot(slot_grp, s2);
+      load_v(g2, v);
+      unpack();
+      next_words();
+      if (!ahead) multiply(slot, buf);
+      scale_v(g2, v);
+      __syncthreads();
+      buf ^= 1;
+    }
+
+    // zero-point terms over the slots: K element 8h + i is slot 8h + i
+    float z[8];
+    *reinterpret_cast<f32x4*>(&z[0]) = *reinterpret_cast<const f32x4*>(&zl[tw + col][8 * h]);
+    *reinterpret_cast<f32x4*>(&z[4]) = *reinterpret_cast<const f32x4*>(&zl[tw + col][8 * h + 4]);
+    bf16x8 zp[3];
+    split_row3(z, zp);
+    const int64_t i = range * LD_TOK + tw + col;
+    float* o = a.out + ((int64_t)s * a.n + i) * d + ch0 + 4 * h;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r0 = 32 * cb + 4 * h + 8 * q;
-        *reinterpret_cast<f32x4*>(o + 8 * q) =
-            f32x4{out[tb][4 * q] + bias[r0], out[tb][4 * q + 1] + bias[r0 + 1], out[tb][4 * q + 2] + bias[r0 + 2],
-                  out[tb][4 * q + 3] + bias[r0 + 3]};
+    for (int cb = 0; cb < 4; ++cb) {
+      bf16x8 yp[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) yp[p] = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[p][32 * cb + col][8 * h]));
+      f32x16 y = {};
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[0], zp[2], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[2], zp[0], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[1], zp[1], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[0], zp[1], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[1], zp[0], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[0], zp[0], y, 0, 0, 0);
+      // lane (h, col): rows 8q + 4h + r = channels, column col = token
+      if (i < a.n) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias[32 * cb + 8 * q + 4 * h]);
+          f32x4 r;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) r[j] = (out[cb][4 * q + j] + y[4 * q + j]) + b4[j];
+          *reinterpret_cast<f32x4*>(o + 32 * cb + 8 * q) = r;
+        }
       }
     }
   }
@@ -553,8 +680,14 @@ hipError_t launch_layer_encode(const LayerEncodeArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_layer_decode(const LayerDecodeArgs& a, hipStream_t st) {
-  const dim3 grid(xcd_major_grid((int)((a.n + LD_TOK * LD_NT - 1) / (LD_TOK * LD_NT)), a.d / LD_CH), 1, a.n_streams);
-  hipLaunchKernelGGL(layer_decode_kernel, grid, dim3(512), 0, st, a);
+  // one workgroup per CU (LDS): every workgroup walks as many ranges as the longest
+  const int64_t ranges = (a.n + LD_TOK - 1) / LD_TOK, nb = a.d / LD_CH;
+  const int64_t each = (ranges * nb * a.n_streams + 255) / 256;
+  const dim3 grid((unsigned)((ranges + each - 1) / each * nb), 1, a.n_streams);
+  if (a.lscale)
+    hipLaunchKernelGGL(layer_decode_kernel<true>, grid, dim3(64 * LD_NW), 0, st, a);
+  else
+    hipLaunchKernelGGL(layer_decode_kernel<false>, grid, dim3(64 * LD_NW), 0, st, a);
   return hipGetLastError();
 }
 
