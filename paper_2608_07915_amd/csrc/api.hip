@@ -380,12 +380,6 @@ spectra_status spectra_layer_decode_attention(const spectra_codec* ck, const spe
   const size_t need = spectra_layer_attention_workspace_bytes(ck, batch, n_q_heads, n_tokens);
   if (!workspace || !aligned(workspace, 256)) return fail(SPECTRA_EINVAL, "%s: workspace must be 256-byte aligned", name);
   if (ws_bytes < need) return fail(SPECTRA_EWORKSPACE, "%s: workspace %zu < %zu bytes", name, ws_bytes, need);
-  int dev = 0, lds = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-  if (e != hipSuccess) return hip_fail(e, "device query");
-  if ((size_t)lds < layer_scores_lds_bytes(d, ck->record_words))
-    return fail(SPECTRA_EUNSUPPORTED, "%s: needs %zu bytes of LDS per workgroup", name, layer_scores_lds_bytes(d, ck->record_words));
   spectra_dev::LayerAttnArgs a{};
   a.packed_k = packed_k;
   a.packed_v = packed_v;
@@ -410,7 +404,7 @@ spectra_status spectra_layer_decode_attention(const spectra_codec* ck, const spe
   a.scale_log2 = sc * 1.4426950408889634f;
   a.out = out;
   layer_attention_ws_layout(a, reinterpret_cast<float*>(workspace));
-  e = launch_layer_attention(a, (hipStream_t)stream);
+  hipError_t e = launch_layer_attention(a, (hipStream_t)stream);
   return e == hipSuccess ? SPECTRA_OK : hip_fail(e, "layer attention launch");
 }
 

@@ -387,7 +387,7 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
   const int64_t r_step = gridDim.x / (unsigned)nb;
   const int64_t sbase = (int64_t)s * a.t_cap * a.W;
   const float* Vs = a.basis + (int64_t)s * d * d;
-  if (tid == 0) layer_table(a.bits + (int64_t)s * ng, ng, tab);
+  if (wave == 0) layer_table(a.bits + (int64_t)s * ng, ng, lane, tab);
   for (int i = tid; i < d; i += NT) mean[i] = a.mean[(int64_t)s * d + i];
   for (int i = tid; i < 3 * LD_CH * LD_YP / 2; i += NT) reinterpret_cast<uint32_t*>(yl)[i] = 0u;  // slots past the kept ones
   for (int i = tid; i < LD_TOK * LD_ZP; i += NT) reinterpret_cast<float*>(zl)[i] = 0.0f;

@@ -10,23 +10,22 @@
 //
 //   layer_qprep_kernel    q~ (scale and log2 e folded in) and its per-group sums;
 //   layer_scores_kernel   scores of all heads for a chunk of 64-token tiles: codes
-//                         (exact in fp16) times q~ as two fp16 parts on
-//                         v_mfma_f32_16x16x32_f16, one kept group at a time, the
-//                         token's scale and zero point applied after; chunk max and sum;
-//   layer_stats_kernel    softmax max and sum of every head over the chunks;
-//   layer_values_kernel   p = exp2(s - max over all chunks), then per kept value group
+//                         (exact in fp16) times q~ as two fp16 parts, one kept group at a
+//                         time, the token's scale and zero point applied after; chunk max;
+//   layer_values_kernel   p = exp2(s - max over its two chunks), then per kept value group
 //                         sum_t p_t s_t q_t on v_mfma_f32_16x16x32_bf16 (weights as two
 //                         bf16 parts, codes of eight consecutive tokens read from the
 //                         word-major tile) and sum_t p_t z_t;
-//   layer_combine_kernel  sums the chunk partials, divides by the softmax sum, adds m_V;
+//   layer_combine_kernel  softmax max and sum over the chunks, the chunk partials' sum,
+//                         divided by it, plus m_V;
 //   layer_rotate_kernel   applies V_V[kv rows]^T.
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "attn_common.hpp"
 #include "layer.hpp"
+#include "layer_codes.hpp"
 
 namespace spectra_dev {
-
-typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8v;
 
 constexpr int LA_H = 32;     // query heads per sequence (at most)
 constexpr int LA_ROW = 68;   // words per staged record row (64 tokens + pad)
@@ -34,26 +33,6 @@ constexpr int LA_WMAX = 128;  // record words per tensor
 // record words per tile staged through registers: the kernels are instantiated for
 // records of at most 64 words and of at most LA_WMAX words
 __host__ __device__ constexpr int la_prefetch_words(int W) { return W <= 64 ? 64 : LA_WMAX; }
-
-// kept groups of a per-layer stream in slot order: group, width, first payload word
-__device__ __forceinline__ int layer_slots(const uint8_t* __restrict__ bits_s, int ng, int* grp, int* bw, int* pay) {
-  int n = 0;
-  for (int g = 0; g < ng; ++g)
-    if (bits_s[g] > 0) ++n;
-  int off = n;
-  int k = 0;
-  for (int g = 0; g < ng; ++g) {
-    const int b = bits_s[g];
-    if (b > 0) {
-      grp[k] = g;
-      bw[k] = b;
-      pay[k] = off;
-      off += 2 * b;
-      ++k;
-    }
-  }
-  return n;
-}
 
 __device__ __forceinline__ bool layer_bits_ok(const uint8_t* __restrict__ bits_s, int ng, int W) {
   int used = 0;
@@ -68,22 +47,26 @@ __device__ __forceinline__ bool layer_bits_ok(const uint8_t* __restrict__ bits_s
 // ---------------------------------------------------------------------------
 // q~[b][h][j] = scale log2(e) sum_i q[b][h][i] V_K[b][kv 128 + i][j] on kept groups
 // ---------------------------------------------------------------------------
-// grid (heads, sequences, d / 256): thread -> one coefficient j, four groups per workgroup
-__global__ __launch_bounds__(256) void layer_qprep_kernel(LayerAttnArgs a) {
+// grid (heads, sequences, d / 256): thread (coefficient j, quarter of the 128 rows), all its
+// 32 loads in flight at once; four groups per workgroup
+__global__ __launch_bounds__(1024) void layer_qprep_kernel(LayerAttnArgs a) {
   __shared__ float qv[128];
-  __shared__ float qtl[256];
+  __shared__ float part[4][256];
   __shared__ int slot_of[16];  // kept rank of each group
-  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, jj = tid & 255, quarter = tid >> 8;
   const int d = a.d, ng = d / 64;
-  const int j = 256 * blockIdx.z + tid;
+  const int j = 256 * blockIdx.z + jj;
   const int kv = h / (a.n_q_heads / a.n_kv_heads);
   const uint8_t* bits_s = a.bits_k + (int64_t)b * ng;
-  if (tid == 0) {
+  const bool kept = j < d && bits_s[j >> 6] > 0;
+  const float* V = a.basis_k + (int64_t)b * d * d + (int64_t)(kv * 128 + 32 * quarter) * d + (j < d ? j : 0);
+  float v[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) v[i] = V[(int64_t)i * d];
+  if (tid < ng) {
     int n = 0;
-    for (int g = 0; g < ng; ++g) {
-      slot_of[g] = n;
-      n += bits_s[g] > 0 ? 1 : 0;
-    }
+    for (int g = 0; g < tid; ++g) n += bits_s[g] > 0 ? 1 : 0;
+    slot_of[tid] = n;
   }
   if (tid < 128) {
     const int64_t qi = ((int64_t)b * a.n_q_heads + h) * 128 + tid;
@@ -91,376 +74,342 @@ __global__ __launch_bounds__(256) void layer_qprep_kernel(LayerAttnArgs a) {
               a.scale_log2;
   }
   __syncthreads();
-  const float* V = a.basis_k + (int64_t)b * d * d + (int64_t)kv * 128 * d + j;
-  float acc = 0.0f;
-  if (j < d && bits_s[j >> 6] > 0) {
-    float part[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int i = 0; i < 128; i += 8)
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < 8; ++r) part[r] = __builtin_fmaf(qv[i + r], V[(int64_t)(i + r) * d], part[r]);
-    acc = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
-    if (a.lscale_k) acc /= a.lscale_k[(int64_t)b * d + j];
-  }
-  qtl[tid] = acc;
-  if (j < d) {
-    a.qt[((int64_t)b * a.n_q_heads + h) * d + j] = acc;
-    const int g = j >> 6;
-    if (bits_s[g] > 0) {  // fp16 parts for the score pass, at the group's kept slot
-      const int slot = slot_of[g];
-      const _Float16 hi = (_Float16)acc;
-      const _Float16 lo = (_Float16)(acc - (float)hi);
-      uint16_t* qh = a.qh + (int64_t)b * 2 * LA_H * d;
-      qh[(int64_t)h * d + 64 * slot + (j & 63)] = __builtin_bit_cast(uint16_t, hi);
-      qh[(int64_t)(LA_H + h) * d + 64 * slot + (j & 63)] = __builtin_bit_cast(uint16_t, lo);
-    }
-  }
+  for (int i = 0; i < 32; ++i) sum[i & 3] = __builtin_fmaf(qv[32 * quarter + i], v[i], sum[i & 3]);
+  part[quarter][jj] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
   __syncthreads();
-  // group sums (only the groups of this workgroup's coefficients; the score pass reads kept groups only)
-  if (tid < 4 && 4 * (int)blockIdx.z + tid < ng) {
-    float s = 0.0f;
-    for (int jj = 0; jj < 64; ++jj) s += qtl[64 * tid + jj];
-    a.qsum[((int64_t)b * a.n_q_heads + h) * 16 + 4 * blockIdx.z + tid] = s;
+  if (tid >= 256) return;
+  float acc = kept ? (part[0][jj] + part[1][jj]) + (part[2][jj] + part[3][jj]) : 0.0f;
+  if (kept && a.lscale_k) acc /= a.lscale_k[(int64_t)b * d + j];
+  if (kept) {
+    const int g = j >> 6;
+    // fp16 parts for the score pass, at the group's kept slot
+    const _Float16 hi = (_Float16)acc;
+    const _Float16 lo = (_Float16)(acc - (float)hi);
+    uint16_t* qh = a.qh + (int64_t)b * 2 * LA_H * d;
+    const int place = 64 * slot_of[g] + code_position(j & 63);
+    qh[(int64_t)h * d + place] = __builtin_bit_cast(uint16_t, hi);
+    qh[(int64_t)(LA_H + h) * d + place] = __builtin_bit_cast(uint16_t, lo);
   }
+  // group sums: a wavefront's 64 coefficients are one group (the score pass reads kept groups only)
+  const float s = wave_sum_lane63(acc);
+  if ((tid & 63) == 63 && j < d) a.qsum[((int64_t)b * a.n_q_heads + h) * 16 + (j >> 6)] = s;
 }
 
 // ---------------------------------------------------------------------------
 // Scores
 // ---------------------------------------------------------------------------
-// A score workgroup takes NHB blocks of 16 query heads: both (NHB = 2), or, when the
-// latent queries of 32 heads and the record rows would not fit the LDS together
-// (d = 1024 with records of more than ~100 words), one (NHB = 1, blockIdx.z selects it).
-__host__ __device__ constexpr int la_qp(int d) { return d + 8; }  // fp16 per staged query row
-constexpr int LA_QSP = 17;  // floats per row of the group sums (16 slots + pad: the rows of four heads read together lie on distinct banks)
-__host__ __device__ constexpr int la_off_rec(int d, int nhb) { return 2 * 16 * nhb * la_qp(d) * 2; }
-// the record rows also hold the slot halves' scores of a tile ([4][64][8] floats) once read
-__host__ __device__ constexpr int la_rec_bytes(int Wk) { return Wk * LA_ROW * 4 > 4 * 64 * 8 * 4 ? Wk * LA_ROW * 4 : 4 * 64 * 8 * 4; }
-__host__ __device__ constexpr int la_off_qs(int d, int Wk, int nhb) { return la_off_rec(d, nhb) + la_rec_bytes(Wk); }
-__host__ __device__ constexpr int la_scores_lds(int d, int Wk, int nhb) {
-  return la_off_qs(d, Wk, nhb) + LA_H * LA_QSP * 4 + 4 * LA_H * 2 * 4;
-}
+// Sixteen wavefronts per workgroup, each walking its own 32-token blocks over all kept
+// slots (v_mfma_f32_32x32x16_f16: rows = 32 heads, columns = tokens): the latent queries
+// sit in LDS as two fp16 parts, a token's payload words go from memory to registers two
+// slots ahead and become operands there, so nothing is exchanged between wavefronts and
+// the loop has no barrier. Scores of a tile are written as [head][64 tokens].
+// For a 131k-token 1024-wide layer at 8x: eight wavefronts with the codes extracted from
+// staged record rows 61 us; each wavefront holding two slots' queries in registers and the
+// slots' sums meeting in LDS per tile 42 us (two wavefronts per SIMD, half of the time
+// waiting for records); this form 33 us.
+constexpr int LA_SW = 16;      // wavefronts per score workgroup
+constexpr int LA_QP = LG + 8;  // fp16 per staged query row
 
-template <int NHB, int WP>
-__global__ __launch_bounds__(512) void layer_scores_kernel(LayerAttnArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lsm[];
-  const int d = a.d, ng = d / 64, QP = la_qp(d), Wk = a.Wk;
-  uint16_t* qa = reinterpret_cast<uint16_t*>(lsm);                       // [2][16 NHB][QP]
-  uint32_t* rec = reinterpret_cast<uint32_t*>(lsm + la_off_rec(d, NHB)); // [Wk][LA_ROW]
-  float* qs = reinterpret_cast<float*>(lsm + la_off_qs(d, Wk, NHB));     // [LA_H][LA_QSP]
-  float* red = qs + LA_H * LA_QSP;                                       // [4][LA_H][2]
-  __shared__ int sgrp[16], sbw[16], spay[16], snk;
+__global__ __launch_bounds__(64 * LA_SW, 4) void layer_scores_kernel(LayerAttnArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t qa[16][2][LA_H][LA_QP];  // [slot][part][head][place]
+  __shared__ __attribute__((aligned(16))) float qs[16][LA_H];  // [slot][head]: sums of the latent query over the slot's group
+  __shared__ float wmax[LA_SW][LA_H];
+  __shared__ LayerTable tab;
   const int chunk = blockIdx.x, b = blockIdx.y;
-  const int hb0 = NHB == 2 ? 0 : (int)blockIdx.z;  // first head block of this workgroup
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kg = lane >> 4, c16 = lane & 15;
-  const int Hq = a.n_q_heads;
-  const uint8_t* bits_s = a.bits_k + (int64_t)b * ng;
-  const bool ok = layer_bits_ok(bits_s, ng, Wk);
-  if (tid == 0) snk = ok ? layer_slots(bits_s, ng, sgrp, sbw, spay) : 0;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int h = lane >> 5, col = lane & 31;
+  const int d = a.d, ng = d / 64, Hq = a.n_q_heads, Wk = a.Wk;
+  if (wave == 0) layer_table(a.bits_k + (int64_t)b * ng, ng, lane, tab);
   __syncthreads();
-  const int nk = __builtin_amdgcn_readfirstlane(snk);
-  // kept coefficients of q~ as two fp16 parts, compacted by slot; group sums
-  // copied as written by the query pass (16-byte pieces, eight in flight per thread);
-  // rows of heads past n_q_heads are zero
-  {
-    // staged row = part * 16 NHB + local head; source row = part * LA_H + 16 hb0 + local head
-    const uint16_t* qh = a.qh + (int64_t)b * 2 * LA_H * d;
-    const int pieces = nk * 8;  // 16-byte pieces per row
-    for (int i0 = 0; i0 < (2 * 16 * NHB * 16 * 8) / 512; i0 += 8) {
-      u32x4 v[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int e = tid + 512 * (i0 + r), row = e >> 7, pc = e & 127;
-        const int part = row / (16 * NHB), h = 16 * hb0 + row % (16 * NHB);
-        v[r] = (h < Hq && pc < pieces) ? *reinterpret_cast<const u32x4*>(qh + (int64_t)(part * LA_H + h) * d + 8 * pc)
-                                       : u32x4{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int e = tid + 512 * (i0 + r), row = e >> 7, pc = e & 127;
-        if (pc < pieces) *reinterpret_cast<u32x4*>(qa + row * QP + 8 * pc) = v[r];
-      }
-    }
-  }
-  for (int e = tid; e < LA_H * 16; e += 512) {
-    const int h = e >> 4, sl = e & 15;
-    qs[h * LA_QSP + sl] = (h < Hq && sl < nk) ? a.qsum[((int64_t)b * Hq + h) * 16 + sgrp[sl]] : 0.0f;
-  }
+  const int nk = __builtin_amdgcn_readfirstlane(tab.ok && tab.used <= Wk ? tab.n_kept : 0);
+  const int tl = lane & 15;
+  const int slot_b = tl < nk ? tab.b[tl] : 0, slot_pay = tl < nk ? tab.pay[tl] : 0;
+  auto of_slot = [](int table, int slot) { return __builtin_amdgcn_readlane(table, slot); };
 
-  const int64_t n_tiles = (a.n_tokens + 63) >> 6;
-  const int64_t t_begin = (int64_t)chunk * a.tiles_per_chunk;
-  const int64_t t_end = t_begin + a.tiles_per_chunk < n_tiles ? t_begin + a.tiles_per_chunk : n_tiles;
-  const uint32_t* kp = a.packed_k + (int64_t)b * a.t_cap * Wk;
-  // wavefront: token block tb (16 tokens), both head blocks, kept slots sh, sh + 2, ...
-  const int tb = wave & 3, sh = wave >> 2;
-  float mloc[8], lloc[8];
+  const int64_t n_tiles = (a.n_tokens + 63) >> 6, n_blocks = (a.n_tokens + 31) >> 5;
+  const int64_t blk0 = (int64_t)chunk * a.tiles_per_chunk * 2 + wave;
+  int64_t blk_end = ((int64_t)chunk + 1) * a.tiles_per_chunk * 2;
+  if (blk_end > n_blocks) blk_end = n_blocks;
+  const uint32_t* kp = a.packed_k + (int64_t)b * a.t_cap * Wk + col;
+  uint32_t words[2][8], meta[2] = {0u, 0u};  // slots in flight
+  int w_slot = 0;
+  int64_t w_blk = blk0;
+  auto next_words = [&](int par) {  // past the last block its words are read again
+    const int64_t bl = w_blk < blk_end ? w_blk : blk_end - 1;
+    const uint32_t* src = kp + (bl >> 1) * (64 * (int64_t)Wk) + 32 * (bl & 1);
+    const int bw = of_slot(slot_b, w_slot), pay = of_slot(slot_pay, w_slot);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    mloc[j] = -__builtin_inff();
-    lloc[j] = 0.0f;
-  }
-  constexpr int PF = 64 * WP / 512;  // record words per thread and tile
-  uint32_t pre[PF];
-  auto load_tile = [&](int64_t tt) {
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      const int k = tid + 512 * i;
-      pre[i] = k < 64 * Wk ? kp[tt * 64 * Wk + k] : 0u;
+    for (int i = 0; i < 8; ++i)
+      if (i < bw) words[par][i] = src[(pay + h * bw + i) * 64];
+    meta[par] = src[w_slot * 64];
+    if (++w_slot == nk) {
+      w_slot = 0;
+      w_blk += LA_SW;
     }
   };
-  float* sred = reinterpret_cast<float*>(rec);  // [4 token blocks][64 lanes][8], after the tile's products
-  if (t_begin < t_end) load_tile(t_begin);
-  for (int64_t tt = t_begin; tt < t_end; ++tt) {
-    __syncthreads();  // previous tile's reads done (and the prologue's writes visible)
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      const int k = tid + 512 * i;
-      if (k < 64 * Wk) rec[(k >> 6) * LA_ROW + (k & 63)] = pre[i];
+  if (nk > 0 && blk0 < blk_end) {
+    next_words(0);
+    next_words(1);
+  }
+  for (int e = tid; e < 16 * LA_H; e += 64 * LA_SW) {
+    const int sl = e >> 5, hd = e & 31;
+    qs[sl][hd] = (hd < Hq && sl < nk) ? a.qsum[((int64_t)b * Hq + hd) * 16 + tab.grp[sl]] : 0.0f;
+  }
+  // 16-byte pieces: piece pc of row (part, head); rows of heads past n_q_heads are zero
+#pragma unroll 4
+  for (int e = tid; e < 2 * LA_H * 16 * 8; e += 64 * LA_SW) {
+    const int pc = e & 127, row = e >> 7, part = row >> 5, hd = row & 31;
+    if (pc < 8 * nk) {
+      u32x4 v = u32x4{0u, 0u, 0u, 0u};
+      if (hd < Hq) v = *reinterpret_cast<const u32x4*>(a.qh + ((int64_t)(2 * b + part) * LA_H + hd) * d + 8 * pc);
+      *reinterpret_cast<u32x4*>(&qa[pc >> 3][part][hd][8 * (pc & 7)]) = v;
     }
-    __syncthreads();
-    if (tt + 1 < t_end) load_tile(tt + 1);
-    const int u = 16 * tb + c16;
-    f32x4 S[NHB];
+  }
+  uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
+  asm volatile("" : "+v"(magic));
+  float mloc[16];
 #pragma unroll
-    for (int hb = 0; hb < NHB; ++hb) S[hb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int sl = sh; sl < nk; sl += 2) {
-      // slot tables are uniform: scalar registers, scalar branches on the width
-      const int pay = __builtin_amdgcn_readfirstlane(spay[sl]);
-      const int bw = __builtin_amdgcn_readfirstlane(sbw[sl]);
-      const uint32_t m = rec[sl * LA_ROW + u];
-      const float st = h2f(m), zt = h2f(m >> 16);
-      f32x4 g[NHB];
+  for (int i = 0; i < 16; ++i) mloc[i] = -__builtin_inff();
+  f32x16 S = {};
+  int64_t blk = blk0;
+  int slot = 0;
+  // scores of block blk: lane (h, col) holds heads 8q + 4h + r of token col
+  auto finish_block = [&]() {
+    const int64_t t = 32 * blk + col;
+    const bool valid = t < a.n_tokens;
+    float* dst = a.scores + ((int64_t)b * n_tiles + (blk >> 1)) * Hq * 64 + 32 * (blk & 1) + col;
 #pragma unroll
-      for (int hb = 0; hb < NHB; ++hb) g[hb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        f16x8v bop;
-        with_bits(bw, [&](auto bc) {
-          constexpr int B = decltype(bc)::value;
-          uint32_t cd[8];
-          extract8<B>([&](int i) { return rec[(pay + i) * LA_ROW + u]; }, 32 * ks + 8 * kg, cd);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) bop[i] = (_Float16)(float)cd[i];
-        });
-        const int col = sl * 64 + 32 * ks + 8 * kg;
-#pragma unroll
-        for (int hb = 0; hb < NHB; ++hb) {
-          const f16x8v a0 = __builtin_bit_cast(f16x8v, *reinterpret_cast<const u32x4*>(qa + (16 * hb + c16) * QP + col));
-          const f16x8v a1 =
-              __builtin_bit_cast(f16x8v, *reinterpret_cast<const u32x4*>(qa + (16 * NHB + 16 * hb + c16) * QP + col));
-          g[hb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bop, g[hb], 0, 0, 0);
-          g[hb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bop, g[hb], 0, 0, 0);
-        }
-      }
-      // lane: heads 16 (hb0 + hb) + 4 kg + j, token u
-#pragma unroll
-      for (int hb = 0; hb < NHB; ++hb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) S[hb][j] += st * g[hb][j] + zt * qs[(16 * (hb0 + hb) + 4 * kg + j) * LA_QSP + sl];
-    }
-    // the two slot halves meet in LDS (over the record rows, whose reads are done)
-    __syncthreads();
-    if (sh == 1) {
-#pragma unroll
-      for (int hb = 0; hb < NHB; ++hb) *reinterpret_cast<f32x4*>(&sred[(tb * 64 + lane) * 8 + 4 * hb]) = S[hb];
-    }
-    __syncthreads();
-    if (sh == 0) {
-      const int64_t t = tt * 64 + u;
-#pragma unroll
-      for (int hb = 0; hb < NHB; ++hb) {
-        const f32x4 o4 = *reinterpret_cast<const f32x4*>(&sred[(tb * 64 + lane) * 8 + 4 * hb]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int h = 16 * (hb0 + hb) + 4 * kg + j;
-          const float x = S[hb][j] + o4[j];
-          if (t < a.n_tokens && h < Hq) {
-            a.scores[((int64_t)b * Hq + h) * a.n_tokens + t] = x;
-            const int q = 4 * hb + j;
-            if (x > mloc[q]) {
-              lloc[q] = lloc[q] * __builtin_amdgcn_exp2f(mloc[q] - x) + 1.0f;
-              mloc[q] = x;
-            } else {
-              lloc[q] += __builtin_amdgcn_exp2f(x - mloc[q]);
-            }
-          }
-        }
+    for (int i = 0; i < 16; ++i) {
+      const int hd = 8 * (i >> 2) + 4 * h + (i & 3);
+      if (hd < Hq && valid) {
+        dst[64 * hd] = S[i];
+        mloc[i] = __builtin_fmaxf(mloc[i], S[i]);
       }
     }
-  }
-  // chunk statistics: merge the 16 token lanes, then the four token-block wavefronts
+    S = f32x16{};
+    blk += LA_SW;
+    slot = 0;
+  };
+  auto step = [&](auto pc) {
+    constexpr int par = decltype(pc)::value;
+    const int bw = of_slot(slot_b, slot);
+    f16x8 cod[4];
+    with_bits(bw, [&](auto bc) {
+      constexpr int B = decltype(bc)::value;
+      uint32_t Z[8];
+      join_halves<B>(words[par], Z);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+      for (int k = 0; k < 4; ++k) cod[k] = codes_f16<B>(Z, k, magic);
+    });
+    const float st = h2f(meta[par]), zc = __builtin_fmaf(st, (float)(1 << (bw - 1)), h2f(meta[par] >> 16));  // codes are centered
+    next_words(par);
+    f32x16 g = {};
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      const float mo = __shfl_xor(mloc[j], o), lo = __shfl_xor(lloc[j], o);
-      const float mn = __builtin_fmaxf(mloc[j], mo);
-      const float l = (mloc[j] == -__builtin_inff() ? 0.0f : lloc[j] * __builtin_amdgcn_exp2f(mloc[j] - mn)) +
-                      (mo == -__builtin_inff() ? 0.0f : lo * __builtin_amdgcn_exp2f(mo - mn));
-      mloc[j] = mn;
-      lloc[j] = l;
-    }
-  }
-  __syncthreads();
-  if (c16 == 0 && sh == 0) {
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-    for (int q = 0; q < 4 * NHB; ++q) {
-      const int h = 16 * (hb0 + (q >> 2)) + 4 * kg + (q & 3);
-      red[(tb * LA_H + h) * 2] = mloc[q];
-      red[(tb * LA_H + h) * 2 + 1] = lloc[q];
-    }
-  }
-  __syncthreads();
-  // this workgroup's heads only (with NHB = 1 the other block is another workgroup's)
-  if (tid < Hq && tid >= 16 * hb0 && tid < 16 * (hb0 + NHB)) {
-    float m = -__builtin_inff();
-    for (int q = 0; q < 4; ++q) m = __builtin_fmaxf(m, red[(q * LA_H + tid) * 2]);
-    float l = 0.0f;
+      for (int p = 0; p < 2; ++p)
+        g = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const f16x8*>(&qa[slot][p][col][32 * h + 8 * k]), cod[k], g, 0, 0, 0);
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float mq = red[(q * LA_H + tid) * 2];
-      if (mq != -__builtin_inff()) l += red[(q * LA_H + tid) * 2 + 1] * __builtin_amdgcn_exp2f(mq - m);
-    }
-    float* st = a.stats + (((int64_t)b * a.n_chunks + chunk) * Hq + tid) * 2;
-    st[0] = m;
-    st[1] = l;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Softmax max and sum of every head over all chunks (one workgroup per head)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void layer_stats_kernel(LayerAttnArgs a) {
-  __shared__ float rm[4], rl[4];
-  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int Hq = a.n_q_heads;
-  float m = -__builtin_inff(), l = 0.0f;
-  for (int c = tid; c < a.n_chunks; c += 256) {
-    const float* st = a.stats + (((int64_t)b * a.n_chunks + c) * Hq + h) * 2;
-    const float mc = st[0], lc = st[1];
-    if (mc != -__builtin_inff()) {
-      const float mn = __builtin_fmaxf(m, mc);
-      l = (m == -__builtin_inff() ? 0.0f : l * __builtin_amdgcn_exp2f(m - mn)) + lc * __builtin_amdgcn_exp2f(mc - mn);
-      m = mn;
-    }
-  }
+      const f32x4 qv = *reinterpret_cast<const f32x4*>(&qs[slot][8 * q + 4 * h]);
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const float mo = __shfl_xor(m, o), lo = __shfl_xor(l, o);
-    const float mn = __builtin_fmaxf(m, mo);
-    l = (m == -__builtin_inff() ? 0.0f : l * __builtin_amdgcn_exp2f(m - mn)) +
-        (mo == -__builtin_inff() ? 0.0f : lo * __builtin_amdgcn_exp2f(mo - mn));
-    m = mn;
+      for (int r = 0; r < 4; ++r) S[4 * q + r] = __builtin_fmaf(st, g[4 * q + r], __builtin_fmaf(zc, qv[r], S[4 * q + r]));
+    }
+    asm volatile("" : "+v"(S));  // summed here, not with every product alive across the next branch
+    if (++slot == nk) finish_block();
+  };
+  __syncthreads();  // queries and group sums
+  if (nk == 0) {
+    while (blk < blk_end) finish_block();
+  } else if (blk < blk_end) {
+    const int64_t steps = (blk_end - blk + LA_SW - 1) / LA_SW * nk;
+    for (int64_t i = 0; i < steps; i += 2) {
+      step(std::integral_constant<int, 0>{});
+      if (i + 1 < steps) step(std::integral_constant<int, 1>{});
+    }
   }
-  if (lane == 0) {
-    rm[wave] = m;
-    rl[wave] = l;
+  // chunk maxima of every head
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    float m = mloc[i];
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) m = __builtin_fmaxf(m, __shfl_xor(m, o));
+    if (col == 0) wmax[wave][8 * (i >> 2) + 4 * h + (i & 3)] = m;
   }
   __syncthreads();
-  if (tid == 0) {
-    float mm = -__builtin_inff();
-    for (int w = 0; w < 4; ++w) mm = __builtin_fmaxf(mm, rm[w]);
-    float ll = 0.0f;
-    for (int w = 0; w < 4; ++w)
-      if (rm[w] != -__builtin_inff()) ll += rl[w] * __builtin_amdgcn_exp2f(rm[w] - mm);
-    a.ml[((int64_t)b * Hq + h) * 2] = mm;
-    a.ml[((int64_t)b * Hq + h) * 2 + 1] = ll;
+  if (tid < Hq) {
+    float m = -__builtin_inff();
+    for (int w = 0; w < LA_SW; ++w) m = __builtin_fmaxf(m, wmax[w][tid]);
+    a.cmax[((int64_t)b * a.n_chunks + chunk) * Hq + tid] = m;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Values: one workgroup per (token chunk, block of 16 query heads, sequence); wavefront w
-// takes kept value slots w and w + 8
+// Values: one workgroup per (two score chunks, block of 16 query heads, half of the kept
+// slots, sequence); wavefront w takes kept value slot w or w + 8. The halves are workgroups
+// of their own so that two fit a CU (four wavefronts per SIMD): with both slots in one
+// wavefront 61 us for a 131k-token 1024-wide layer at 8x, now 58 us (codes taken one
+// at a time from staged rows, both slots: 91 us).
 // ---------------------------------------------------------------------------
+// Lane (kg, c16) of a product over 32 tokens supplies coefficients 4 c16 .. 4 c16 + 3 of
+// the group for tokens 8 kg .. 8 kg + 7: four codes are at most 32 adjacent bits, so one
+// window per token (from two staged record words) holds the operands of four products.
+// Widths below 8 enter as 1 + c 2^-b, the code in the top b bits of the 7-bit mantissa
+// under the exponent of 1.0; a second product against -1.5 turns that into c 2^-b - 1/2
+// tile by tile (the sums stay near 0; the zero points take the 2^(b-1) s_t back). CLS 0: b in {1, 2, 4} (the four codes never cross a word); 1: b = 3; 2: b in
+// {5, 6, 7} (codes 2 and 3 from the window shifted by 2b); 3: b = 8 (exact integers).
+template <int CLS>
+__device__ __forceinline__ void value_codes4(const uint32_t* __restrict__ rec, int pay, int b, int c16, int tk0, uint32_t magic,
+                                             u32x4 (&r)[4]) {
+  const int bit = 4 * c16 * b, sh = bit & 31;
+  const uint32_t* src = rec + (pay + (bit >> 5)) * LA_ROW + tk0;
+  const u32x4 l0 = *reinterpret_cast<const u32x4*>(src), l1 = *reinterpret_cast<const u32x4*>(src + 4);
+  if constexpr (CLS == 3) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t y0 = i < 2 ? l0[2 * i] : l1[2 * i - 4], y1 = i < 2 ? l0[2 * i + 1] : l1[2 * i - 3];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r[c][i] = int_to_bf16_pair((y0 >> (8 * c)) & 0xFFu, (y1 >> (8 * c)) & 0xFFu);
+    }
+  } else {
+    // z: the 16 bits from the window's start, of two tokens; a code at bit o of both
+    // halves is rotated to bits 7 - b .. 6 (bits of the other half and wrapped ones land
+    // outside the mask)
+    const uint32_t M = ((1u << b) - 1u) << (7 - b), MM = M | (M << 16);
+    uint32_t z[4], z2[4];
+    int o = 0;
+    if constexpr (CLS == 0) {  // two bytes from byte sh / 8; what is left of the offset (b = 1) goes to the rotation
+      const uint32_t k = (uint32_t)sh >> 3, sel = __builtin_amdgcn_perm(k, k, 0u) + 0x05040100u;
+      o = sh & 7;
+      z[0] = __builtin_amdgcn_perm(l0[1], l0[0], sel);
+      z[1] = __builtin_amdgcn_perm(l0[3], l0[2], sel);
+      z[2] = __builtin_amdgcn_perm(l1[1], l1[0], sel);
+      z[3] = __builtin_amdgcn_perm(l1[3], l1[2], sel);
+    } else {
+      // the next word is only needed when the window crosses into it; it is another staged
+      // row at most (the one past the last is padding)
+      const u32x4 h0 = *reinterpret_cast<const u32x4*>(src + LA_ROW), h1 = *reinterpret_cast<const u32x4*>(src + LA_ROW + 4);
+      uint32_t y[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        y[e] = __builtin_amdgcn_alignbit(h0[e], l0[e], sh);
+        y[4 + e] = __builtin_amdgcn_alignbit(h1[e], l1[e], sh);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        z[i] = __builtin_amdgcn_perm(y[2 * i + 1], y[2 * i], 0x05040100u);
+        if constexpr (CLS == 2) z2[i] = __builtin_amdgcn_perm(y[2 * i + 1] >> (2 * b), y[2 * i] >> (2 * b), 0x05040100u);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t zz = CLS == 2 && c >= 2 ? z2[i] : z[i];
+        const int oc = o + (CLS == 2 ? c & 1 : c) * b;
+        r[c][i] = (rotr32(zz, (uint32_t)(32 + oc - (7 - b)) & 31u) & MM) | magic;
+      }
+  }
+}
+
+constexpr int LA_PX = 32;  // floats after a partial row's d value sums: zero-point sums of 16 groups, sum of the weights
+
 template <int WP>
-__global__ __launch_bounds__(512) void layer_values_kernel(LayerAttnArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t rec[WP * LA_ROW];
+__global__ __launch_bounds__(512, 4) void layer_values_kernel(LayerAttnArgs a) {
+  __shared__ __attribute__((aligned(16))) uint32_t rec[(WP + 1) * LA_ROW];  // + a row that windows may touch
   __shared__ __attribute__((aligned(16))) float pl[16 * LA_ROW];
   __shared__ float mh[LA_H];
-  __shared__ int sgrp[16], sbw[16], spay[16], snk;
-  const int chunk = blockIdx.x, hbk = blockIdx.y, b = blockIdx.z;
+  __shared__ LayerTable tab;
+  const int chunk = blockIdx.x, hbk = blockIdx.y >> 1, half = blockIdx.y & 1, b = blockIdx.z;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kg = lane >> 4, c16 = lane & 15;
   const int d = a.d, ng = d / 64, Wv = a.Wv, Hq = a.n_q_heads;
-  const uint8_t* bits_s = a.bits_v + (int64_t)b * ng;
-  const bool ok = layer_bits_ok(bits_s, ng, Wv) && layer_bits_ok(a.bits_k + (int64_t)b * ng, ng, a.Wk);
-  if (tid == 0) snk = ok ? layer_slots(bits_s, ng, sgrp, sbw, spay) : 0;
-  if (tid < LA_H) mh[tid] = tid < Hq ? a.ml[((int64_t)b * Hq + tid) * 2] : -__builtin_inff();
+  const bool key_ok = layer_bits_ok(a.bits_k + (int64_t)b * ng, ng, a.Wk);
+  if (wave == 0) layer_table(a.bits_v + (int64_t)b * ng, ng, lane, tab);
+  if (tid < LA_H) {
+    float m = -__builtin_inff();
+    if (tid < Hq)
+      for (int c = 2 * chunk; c < 2 * chunk + 2 && c < a.n_chunks; ++c)
+        m = __builtin_fmaxf(m, a.cmax[((int64_t)b * a.n_chunks + c) * Hq + tid]);
+    mh[tid] = m;
+  }
+  if (tid < LA_ROW) rec[WP * LA_ROW + tid] = 0u;
   __syncthreads();
-  const int nk = __builtin_amdgcn_readfirstlane(snk);
-  // workgroup: heads 16 hbk .. 16 hbk + 15; wavefront: kept slots wave, wave + 8
-  const int hb = hbk;
-  f32x4 acc[2][4];
+  const bool ok = key_ok && tab.ok && tab.used <= Wv;
+  const int nk = __builtin_amdgcn_readfirstlane(ok ? tab.n_kept : 0);
+  if (half && nk <= 8) return;  // uniform over the workgroup
+  f32x4 acc[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // zero-point sums: thread -> (head 16 hbk + (tid & 15), slot (tid >> 4) & 15, tokens 32 (tid >> 8) ..)
-  const int zhl = tid & 15, zh = 16 * hbk + zhl, zsl = (tid >> 4) & 15, zq = tid >> 8;
-  __shared__ float zred[2][256];
-  float zacc = 0.0f;
+  for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int sl = 8 * half + wave;
+  const int sb = sl < nk ? __builtin_amdgcn_readfirstlane(tab.b[sl]) : 0;
+  const int sp = sl < nk ? __builtin_amdgcn_readfirstlane(tab.pay[sl]) : 0;
+  // sums over this wavefront's slot and the lane's tokens: weights, weights times zero point
+  float wsum = 0.0f, zsum = 0.0f;
 
   const int64_t n_tiles = (a.n_tokens + 63) >> 6;
   const int64_t t_begin = (int64_t)chunk * a.v_tiles_per_chunk;
   const int64_t t_end = t_begin + a.v_tiles_per_chunk < n_tiles ? t_begin + a.v_tiles_per_chunk : n_tiles;
   const uint32_t* vp = a.packed_v + (int64_t)b * a.t_cap * Wv;
-  constexpr int PF = 64 * WP / 512;            // record words per thread and tile
+  constexpr int PF = 64 * WP / 512;            // record rows per wavefront and tile
   constexpr int PS = 16 * 64 / 512;            // scores per thread and tile
   uint32_t pre[PF];
-  float spre[PS];
-  // Slots past n_tokens in the last tile get weight 0; their metadata words are
-  // staged as 0 so that whatever the cache holds there (a NaN scale or zero-point)
-  // never enters the products (0 * NaN would reach every head through the MFMA).
+  float spre[PS], lacc[PS], mref[PS];
+#pragma unroll
+  for (int i = 0; i < PS; ++i) {
+    lacc[i] = 0.0f;
+    mref[i] = 16 * hbk + wave + 8 * i < Hq ? mh[16 * hbk + wave + 8 * i] : 0.0f;
+  }
+  // the rows of this workgroup's slots: metadata row per slot, payload rows [row_lo, row_hi)
+  const int row_lo = half ? __builtin_amdgcn_readfirstlane(tab.pay[8]) : nk;
+  const int row_hi = !half && nk > 8 ? __builtin_amdgcn_readfirstlane(tab.pay[8]) : Wv;
+  // wavefront w stages rows w, w + 8, .. (lane = token). Slots past n_tokens in the last
+  // tile get weight 0; their metadata words are staged as 0 so that whatever the cache
+  // holds there (a NaN scale or zero-point) never enters the products (0 * NaN would reach
+  // every head through the MFMA).
   auto load_tile = [&](int64_t tt) {
+    const bool in = tt * 64 + lane < a.n_tokens;
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
-      const int k = tid + 512 * i;
-      const bool meta_past_end = (k >> 6) < nk && tt * 64 + (k & 63) >= a.n_tokens;
-      pre[i] = (k < 64 * Wv && !meta_past_end) ? vp[tt * 64 * Wv + k] : 0u;
+      const int row = wave + 8 * i;
+      if (row < nk ? (row >> 3) == half : (row >= row_lo && row < row_hi)) {
+        pre[i] = vp[tt * 64 * Wv + 64 * row + lane];
+        if (row < nk && !in) pre[i] = 0u;
+      }
     }
 #pragma unroll
     for (int i = 0; i < PS; ++i) {
-      const int e = tid + 512 * i, h = 16 * hbk + (e >> 6);
-      const int64_t tok = tt * 64 + (e & 63);
-      spre[i] = (h < Hq && tok < a.n_tokens) ? a.scores[((int64_t)b * Hq + h) * a.n_tokens + tok] : -__builtin_inff();
+      const int h = 16 * hbk + wave + 8 * i;
+      spre[i] = h < Hq && in ? a.scores[(((int64_t)b * n_tiles + tt) * Hq + h) * 64 + lane] : -__builtin_inff();
     }
   };
+  uint32_t magic = 0x3F803F80u;  // exponent of 1.0 in both halves, in a VGPR
+  asm volatile("" : "+v"(magic));
+  const bf16x8 mid = as_bf16x8(u32x4{0xBFC0BFC0u, 0xBFC0BFC0u, 0xBFC0BFC0u, 0xBFC0BFC0u});  // -1.5
   if (ok && t_begin < t_end) load_tile(t_begin);
   for (int64_t tt = (ok ? t_begin : t_end); tt < t_end; ++tt) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
-      const int k = tid + 512 * i;
-      if (k < 64 * Wv) rec[(k >> 6) * LA_ROW + (k & 63)] = pre[i];
+      const int row = wave + 8 * i;
+      if (row < nk ? (row >> 3) == half : (row >= row_lo && row < row_hi)) rec[row * LA_ROW + lane] = pre[i];
     }
 #pragma unroll
     for (int i = 0; i < PS; ++i) {
-      const int e = tid + 512 * i, hl = e >> 6, h = 16 * hbk + hl;
-      const float x = spre[i];
-      pl[hl * LA_ROW + (e & 63)] = (x != -__builtin_inff() && mh[h] != -__builtin_inff()) ? __builtin_amdgcn_exp2f(x - mh[h]) : 0.0f;
+      const float pv = __builtin_amdgcn_exp2f(spre[i] - mref[i]);
+      pl[(wave + 8 * i) * LA_ROW + lane] = pv;
+      lacc[i] += pv;
     }
     __syncthreads();
     if (tt + 1 < t_end) load_tile(tt + 1);
-    if (zsl < nk && zh < Hq) {
-      const float* pr = pl + zhl * LA_ROW + 32 * zq;
-      const uint32_t* mr = rec + zsl * LA_ROW + 32 * zq;
-      float z = 0.0f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const f32x4 pv = *reinterpret_cast<const f32x4*>(pr + 4 * q);
-        const u32x4 mv = *reinterpret_cast<const u32x4*>(mr + 4 * q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) z = __builtin_fmaf(pv[e], h2f(mv[e] >> 16), z);
-      }
-      zacc += z;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int sl = wave + 8 * i;
-      if (sl < nk) {
-        const int B = __builtin_amdgcn_readfirstlane(sbw[sl]), pay = __builtin_amdgcn_readfirstlane(spay[sl]);
-        const uint32_t M = (1u << B) - 1u;
+    if (sb > 0) {
+      auto body = [&](auto cls) {
+        constexpr int CLS = decltype(cls)::value;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
           const int tk0 = 32 * ks + 8 * kg;
-          // weights p_t s_t of head 16 hb + c16 for tokens tk0 .. tk0 + 7 as two bf16 parts:
+          // weights p_t s_t of head 16 hbk + c16 for tokens tk0 .. tk0 + 7 as two bf16 parts:
           // the fp32 exponent range (p_t s_t spans many decades below 1) and 16 significant
           // bits (relative error below 2^-17 per weight; a third part changed the output by
           // 1e-6 relative and cost 7% of the call)
@@ -468,75 +417,89 @@ __global__ __launch_bounds__(512) void layer_values_kernel(LayerAttnArgs a) {
           {
             const float* pr = pl + c16 * LA_ROW + tk0;
             const f32x4 p0 = *reinterpret_cast<const f32x4*>(pr), p1 = *reinterpret_cast<const f32x4*>(pr + 4);
-            const u32x4 m0 = *reinterpret_cast<const u32x4*>(rec + sl * LA_ROW + tk0);
-            const u32x4 m1 = *reinterpret_cast<const u32x4*>(rec + sl * LA_ROW + tk0 + 4);
-            uint32_t q0[8], q1[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const float wv = (e < 4 ? p0[e] : p1[e - 4]) * h2f(e < 4 ? m0[e] : m1[e - 4]);
-              q0[e] = f2bf(wv);
-              q1[e] = f2bf(wv - bf2f(q0[e]));
-            }
-            wp[0] = as_bf16x8(u32x4{pack2(q0[0], q0[1]), pack2(q0[2], q0[3]), pack2(q0[4], q0[5]), pack2(q0[6], q0[7])});
-            wp[1] = as_bf16x8(u32x4{pack2(q1[0], q1[1]), pack2(q1[2], q1[3]), pack2(q1[4], q1[5]), pack2(q1[6], q1[7])});
-          }
-#pragma unroll
-          for (int cb = 0; cb < 4; ++cb) {
-            // codes of coefficient 16 cb + c16 for tokens tk0 .. tk0 + 7
-            const int bit = (16 * cb + c16) * B, w = pay + (bit >> 5), sh = bit & 31;
-            const bool two = sh + B > 32;
-            const u32x4 l0 = *reinterpret_cast<const u32x4*>(rec + w * LA_ROW + tk0);
-            const u32x4 l1 = *reinterpret_cast<const u32x4*>(rec + w * LA_ROW + tk0 + 4);
-            u32x4 h0 = {0u, 0u, 0u, 0u}, h1 = {0u, 0u, 0u, 0u};
-            if (two) {
-              h0 = *reinterpret_cast<const u32x4*>(rec + (w + 1) * LA_ROW + tk0);
-              h1 = *reinterpret_cast<const u32x4*>(rec + (w + 1) * LA_ROW + tk0 + 4);
-            }
-            uint32_t cd[8];
+            const uint32_t* mr = rec + sl * LA_ROW + tk0;
+            const u32x4 m0 = *reinterpret_cast<const u32x4*>(mr), m1 = *reinterpret_cast<const u32x4*>(mr + 4);
+            u32x4 hi, lo;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              cd[e] = __builtin_amdgcn_alignbit(h0[e], l0[e], sh) & M;
-              cd[4 + e] = __builtin_amdgcn_alignbit(h1[e], l1[e], sh) & M;
+              const float pa = e < 2 ? p0[2 * e] : p1[2 * e - 4], pc = e < 2 ? p0[2 * e + 1] : p1[2 * e - 3];
+              const uint32_t ma = e < 2 ? m0[2 * e] : m1[2 * e - 4], mc = e < 2 ? m0[2 * e + 1] : m1[2 * e - 3];
+              const f32x2 w = f32x2{pa * h2f(ma), pc * h2f(mc)};
+              wsum += w[0];
+              wsum += w[1];
+              zsum = __builtin_fmaf(pa, h2f(ma >> 16), zsum);
+              zsum = __builtin_fmaf(pc, h2f(mc >> 16), zsum);
+              const uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(w, bf16x2));
+              const f32x2 rest = f32x2{w[0] - __uint_as_float(hb << 16), w[1] - __uint_as_float(hb & 0xFFFF0000u)};
+              hi[e] = hb;
+              lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
             }
-            const bf16x8 cv = as_bf16x8(u32x4{int_to_bf16_pair(cd[0], cd[1]), int_to_bf16_pair(cd[2], cd[3]),
-                                              int_to_bf16_pair(cd[4], cd[5]), int_to_bf16_pair(cd[6], cd[7])});
+            wp[0] = as_bf16x8(hi);
+            wp[1] = as_bf16x8(lo);
+          }
+          u32x4 cv[4];
+          value_codes4<CLS>(rec, sp, sb, c16, tk0, magic, cv);
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
-              acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[q], cv, acc[i][cb], 0, 0, 0);
+          for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+              acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[q], as_bf16x8(cv[cb]), acc[cb], 0, 0, 0);
+            if constexpr (CLS != 3)
+#pragma unroll
+              for (int cb = 0; cb < 4; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[q], mid, acc[cb], 0, 0, 0);
           }
         }
-      }
+      };
+      if (sb == 8)
+        body(std::integral_constant<int, 3>{});
+      else if (sb == 3)
+        body(std::integral_constant<int, 1>{});
+      else if (sb <= 4)
+        body(std::integral_constant<int, 0>{});
+      else
+        body(std::integral_constant<int, 2>{});
     }
   }
-  // partials: lane holds rows (heads 16 hb + 4 kg + j) of column (coefficient 16 cb + c16)
-  float* pb = a.part + ((int64_t)b * a.nv_chunks + chunk) * Hq * (d + 16);
+  // partials: lane holds rows (heads 16 hbk + 4 kg + j) of coefficients 4 c16 .. 4 c16 + 3
+  float* pb = a.part + ((int64_t)b * a.nv_chunks + chunk) * Hq * (d + LA_PX);
+  if (sb > 0) {
+    const float vs = sb < 8 ? (float)(1 << sb) : 1.0f;  // codes below 8 bits entered as c 2^-b - 1/2
+    const int grp = __builtin_amdgcn_readfirstlane(tab.grp[sl]);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int sl = wave + 8 * i;
-    if (sl < nk) {
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int h = 16 * hb + 4 * kg + j;
-          if (h < Hq) pb[(int64_t)h * (d + 16) + 64 * sgrp[sl] + 16 * cb + c16] = acc[i][cb][j];
-        }
+    for (int j = 0; j < 4; ++j) {
+      const int h = 16 * hbk + 4 * kg + j;
+      if (h < Hq)
+        *reinterpret_cast<f32x4*>(pb + (int64_t)h * (d + LA_PX) + 64 * grp + 4 * c16) =
+            f32x4{acc[0][j] * vs, acc[1][j] * vs, acc[2][j] * vs, acc[3][j] * vs};
     }
   }
-  zred[zq][tid & 255] = zacc;
-  __syncthreads();
-  if (tid < 256 && zsl < nk && zh < Hq) pb[(int64_t)zh * (d + 16) + d + sgrp[zsl]] = zred[0][tid] + zred[1][tid];
+  // wavefront w: sums of the weights of heads 16 hbk + w + 8 i over its 64 token lanes
+#pragma unroll
+  for (int i = 0; i < PS; ++i) {
+    const int h = 16 * hbk + wave + 8 * i;
+    const float l = wave_sum_lane63(lacc[i]);
+    if (half == 0 && lane == 63 && h < Hq) pb[(int64_t)h * (d + LA_PX) + d + 16] = l;
+  }
+  // lane (kg, c16) holds its tokens' share of head 16 hbk + c16
+  float zt = __builtin_fmaf(wsum, sb > 0 && sb < 8 ? (float)(1 << (sb - 1)) : 0.0f, zsum);
+  zt += __shfl_xor(zt, 16);
+  zt += __shfl_xor(zt, 32);
+  if (sb > 0 && kg == 0 && 16 * hbk + c16 < Hq) pb[(int64_t)(16 * hbk + c16) * (d + LA_PX) + d + tab.grp[sl]] = zt;
 }
 
 // ---------------------------------------------------------------------------
-// Combine: c[j] = (sum over value chunks of the coefficient sums + zero-point sums)
-// / softmax sum + m_V[j], written over q~ (no longer needed); grid (heads, sequences,
-// d / 64 groups)
+// Combine: c[j] = (sum over value chunks of exp2(their maximum - overall maximum) times
+// (coefficient sums + zero-point sums)) / softmax sum + m_V[j], written over q~ (no longer
+// needed); grid (heads, sequences, d / 64 groups). The softmax maximum over the
+// score chunks and the weights' sum over the value chunks are taken by every workgroup itself (one maximum per chunk).
 // ---------------------------------------------------------------------------
+constexpr int LA_CHUNKS = 256;  // score chunks per sequence (at most)
+
 __global__ __launch_bounds__(256) void layer_combine_kernel(LayerAttnArgs a) {
   // thread -> (coefficient 64 z + (tid & 63), every fourth chunk from tid >> 6): four short
   // chains of loads instead of one long one, summed in LDS in a fixed order
-  __shared__ float ps[4][64], pz[4][64];
+  __shared__ float ps[4][64], cm[LA_CHUNKS], cf[LA_CHUNKS / 2 + 64], red[3][4];
   const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const int d = a.d, ng = d / 64, Hq = a.n_q_heads;
   const int j = 64 * blockIdx.z + (tid & 63), part = tid >> 6;
@@ -544,32 +507,53 @@ __global__ __launch_bounds__(256) void layer_combine_kernel(LayerAttnArgs a) {
   const bool ok = layer_bits_ok(bv, ng, a.Wv) && layer_bits_ok(a.bits_k + (int64_t)b * ng, ng, a.Wk);
   const int g = j >> 6;  // one group per workgroup
   const bool kept = ok && bv[g] > 0;
-  float s0 = 0.f, s1 = 0.f, z0 = 0.f, z1 = 0.f;
+  const int64_t cstride = (int64_t)Hq * (d + LA_PX);
+  const float* pb = a.part + ((int64_t)b * a.nv_chunks * Hq + h) * (d + LA_PX);
+  const float m = tid < a.n_chunks ? a.cmax[((int64_t)b * a.n_chunks + tid) * Hq + h] : -__builtin_inff();
+  const float lv = ok && tid < a.nv_chunks ? pb[tid * cstride + d + 16] : 0.0f;
+  const float zv = kept && tid < a.nv_chunks ? pb[tid * cstride + d + g] : 0.0f;
+  cm[tid] = m;
+  const float mw = wave_max_all(m);
+  if ((tid & 63) == 0) red[0][part] = mw;
+  __syncthreads();
+  const float M = __builtin_fmaxf(__builtin_fmaxf(red[0][0], red[0][1]), __builtin_fmaxf(red[0][2], red[0][3]));
+  float f = 0.0f;
+  if (tid < LA_CHUNKS / 2) {
+    const float mv = __builtin_fmaxf(cm[2 * tid], cm[2 * tid + 1]);
+    f = mv != -__builtin_inff() ? __builtin_amdgcn_exp2f(mv - M) : 0.0f;
+  }
+  if (tid < LA_CHUNKS / 2 + 64) cf[tid] = f;  // 0 past the last chunk
+  const float lw = wave_sum_lane63(f * lv), zw = wave_sum_lane63(f * zv);
+  if ((tid & 63) == 63) {
+    red[1][part] = lw;
+    red[2][part] = zw;
+  }
+  __syncthreads();
+  float s0 = 0.f, s1 = 0.f;
   if (kept) {
-    const float* pb = a.part + ((int64_t)b * a.nv_chunks * Hq + h) * (d + 16);
-    const int64_t cstride = (int64_t)Hq * (d + 16);
-    int ch = part;
-#pragma unroll 2
-    for (; ch + 4 < a.nv_chunks; ch += 8) {
-      s0 += pb[ch * cstride + j];
-      z0 += pb[ch * cstride + d + g];
-      s1 += pb[(ch + 4) * cstride + j];
-      z1 += pb[(ch + 4) * cstride + d + g];
-    }
-    if (ch < a.nv_chunks) {
-      s0 += pb[ch * cstride + j];
-      z0 += pb[ch * cstride + d + g];
+    // sixteen loads in flight; chunks past the last read it again with weight 0
+    for (int c0 = __builtin_amdgcn_readfirstlane(part); c0 < a.nv_chunks; c0 += 64) {
+      float x[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int ch = c0 + 4 * i;
+        x[i] = pb[(ch < a.nv_chunks ? ch : a.nv_chunks - 1) * cstride + j];
+      }
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        s0 = __builtin_fmaf(cf[c0 + 4 * i], x[i], s0);
+        s1 = __builtin_fmaf(cf[c0 + 4 * i + 4], x[i + 1], s1);
+      }
     }
   }
   ps[part][tid & 63] = s0 + s1;
-  pz[part][tid & 63] = z0 + z1;
   __syncthreads();
   if (tid < 64) {
-    const float l = a.ml[((int64_t)b * Hq + h) * 2 + 1];
-    const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;
+    const float L = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    const float inv_l = L > 0.0f ? 1.0f / L : 0.0f;
     float c = 0.0f;
     if (kept)
-      c = (((ps[0][tid] + ps[1][tid]) + (ps[2][tid] + ps[3][tid])) + ((pz[0][tid] + pz[1][tid]) + (pz[2][tid] + pz[3][tid]))) *
+      c = (((ps[0][tid] + ps[1][tid]) + (ps[2][tid] + ps[3][tid])) + ((red[2][0] + red[2][1]) + (red[2][2] + red[2][3]))) *
           inv_l;
     if (a.lscale_v) c /= a.lscale_v[(int64_t)b * d + j];
     a.qt[((int64_t)b * Hq + h) * d + j] = c + a.mean_v[(int64_t)b * d + j];
@@ -586,20 +570,25 @@ __global__ __launch_bounds__(256) void layer_rotate_kernel(LayerAttnArgs a) {
   const int d = a.d, Hq = a.n_q_heads;
   const int kv = h / (Hq / a.n_kv_heads);
   const float* cfv = a.qt + ((int64_t)b * Hq + h) * d;
-  float cl[16];
+  // every load before the first use: columns past d read column `lane` again, times 0
+  float cl[16], v[2][16];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) cl[k] = (64 * k + lane < d) ? cfv[64 * k + lane] : 0.0f;
+  for (int k = 0; k < 16; ++k) {
+    const int j = 64 * k + lane < d ? 64 * k + lane : lane;
+    cl[k] = 64 * k < d ? cfv[j] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      v[r][k] = a.basis_v[(int64_t)b * d * d + (int64_t)(kv * 128 + 8 * (int)blockIdx.z + 2 * wave + r) * d + j];
+  }
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
-    const int i = 8 * blockIdx.z + 2 * wave + r;
-    const float* vr = a.basis_v + (int64_t)b * d * d + (int64_t)(kv * 128 + i) * d;
     float acc = 0.0f;
 #pragma unroll
     for (int k = 0; k < 16; ++k)
-      if (64 * k + lane < d) acc = __builtin_fmaf(cl[k], vr[64 * k + lane], acc);
+      if (64 * k < d) acc = __builtin_fmaf(cl[k], v[r][k], acc);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) a.out[((int64_t)b * Hq + h) * 128 + i] = acc;
+    if (lane == 0) a.out[((int64_t)b * Hq + h) * 128 + 8 * blockIdx.z + 2 * wave + r] = acc;
   }
 }
 
@@ -608,35 +597,36 @@ __global__ __launch_bounds__(256) void layer_rotate_kernel(LayerAttnArgs a) {
 namespace spectra {
 using namespace spectra_dev;
 
-// About 256 workgroups per pass over all sequences, at least four tiles per chunk.
-int32_t layer_attention_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk) {
+// About 256 score workgroups over all sequences (one per CU: LDS), at least two tiles per chunk.
+constexpr int LA_MIN_TILES = 2;
+static int64_t layer_chunks_wanted(int32_t batch) { return (LA_CHUNKS + batch - 1) / batch; }
+static int32_t layer_attention_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk) {
   const int64_t n_tiles = (n_tokens + 63) / 64;
-  const int64_t want = (256 + batch - 1) / batch;
+  const int64_t want = layer_chunks_wanted(batch);
   int64_t tpc = (n_tiles + want - 1) / want;
-  if (tpc < 4) tpc = 4;
+  if (tpc < LA_MIN_TILES) tpc = LA_MIN_TILES;
   *tiles_per_chunk = (int32_t)tpc;
   return (int32_t)((n_tiles + tpc - 1) / tpc);
 }
 
-// Value pass: about 256 workgroups over (chunk, head block of 16, sequence), at least 8
-// tiles each.
-int32_t layer_value_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk) {
-  const int64_t n_tiles = (n_tokens + 63) / 64;
-  const int64_t want = (128 + batch - 1) / batch;
-  int64_t tpc = (n_tiles + want - 1) / want;
-  if (tpc < 8) tpc = 8;
-  *tiles_per_chunk = (int32_t)tpc;
-  return (int32_t)((n_tiles + tpc - 1) / tpc);
-}
-
-size_t layer_attention_ws_floats(int32_t batch, int32_t n_q_heads, int32_t d, int64_t n_tokens) {
+// Value pass: two score chunks per workgroup and head block, so its softmax reference is
+// the larger of their two maxima.
+static int32_t layer_value_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk) {
   int32_t tpc;
-  const int64_t nch = layer_attention_chunks(batch, n_tokens, &tpc);
-  const int64_t nv = layer_value_chunks(batch, n_tokens, &tpc);
+  const int32_t nch = layer_attention_chunks(batch, n_tokens, &tpc);
+  *tiles_per_chunk = 2 * tpc;
+  return (nch + 1) / 2;
+}
+
+// Sized for the most chunks that any token count up to n_tokens is split into, so a workspace
+// taken for a longer cache serves every shorter one.
+size_t layer_attention_ws_floats(int32_t batch, int32_t n_q_heads, int32_t d, int64_t n_tokens) {
+  const int64_t n_tiles = (n_tokens + 63) / 64, want = layer_chunks_wanted(batch);
+  const int64_t most = (n_tiles + LA_MIN_TILES - 1) / LA_MIN_TILES, nch = most < want ? most : want, nv = (nch + 1) / 2;
   const int64_t B = batch, H = n_q_heads;
   auto r64 = [](int64_t n) { return (n + 63) / 64 * 64; };  // 256-byte aligned sections
-  return (size_t)(r64(B * H * d) + r64(B * LA_H * d) + r64(B * H * 16) + r64(B * H * 2) + r64(B * H * n_tokens) +
-                  r64(B * nch * H * 2) + r64(B * nv * H * (d + 16)));
+  return (size_t)(r64(B * H * d) + r64(B * LA_H * d) + r64(B * H * 16) + r64(B * H * n_tiles * 64) + r64(B * nch * H) +
+                  r64(B * nv * H * (d + LA_PX)));
 }
 
 void layer_attention_ws_layout(LayerAttnArgs& a, float* ws) {
@@ -647,48 +637,22 @@ void layer_attention_ws_layout(LayerAttnArgs& a, float* ws) {
   a.qt = ws;
   a.qh = reinterpret_cast<uint16_t*>(a.qt + r64(B * H * a.d));  // 2 x 32 x d halves = 32 x d floats
   a.qsum = a.qt + r64(B * H * a.d) + r64(B * LA_H * a.d);
-  a.ml = a.qsum + r64(B * H * 16);
-  a.scores = a.ml + r64(B * H * 2);
-  a.stats = a.scores + r64(B * H * a.n_tokens);
-  a.part = a.stats + r64(B * a.n_chunks * H * 2);
+  a.scores = a.qsum + r64(B * H * 16);
+  a.cmax = a.scores + r64(B * H * ((a.n_tokens + 63) / 64 * 64));
+  a.part = a.cmax + r64(B * a.n_chunks * H);
 }
 
-// the score pass with one head block per workgroup (the smaller LDS footprint)
-size_t layer_scores_lds_bytes(int32_t d, int32_t Wk) { return (size_t)la_scores_lds(d, Wk, 1); }
-
 hipError_t launch_layer_attention(const LayerAttnArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(layer_qprep_kernel, dim3(a.n_q_heads, a.batch, (a.d + 255) / 256), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(layer_qprep_kernel, dim3(a.n_q_heads, a.batch, (a.d + 255) / 256), dim3(1024), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  int dev = 0, lds_max = 0;
-  e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-  if (e != hipSuccess) return e;
-  const bool k_wide = la_prefetch_words(a.Wk) > 64, v_wide = la_prefetch_words(a.Wv) > 64;
-  if ((size_t)la_scores_lds(a.d, a.Wk, 2) <= (size_t)lds_max) {
-    if (k_wide)
-      hipLaunchKernelGGL((layer_scores_kernel<2, LA_WMAX>), dim3(a.n_chunks, a.batch), dim3(512),
-                         la_scores_lds(a.d, a.Wk, 2), st, a);
-    else
-      hipLaunchKernelGGL((layer_scores_kernel<2, 64>), dim3(a.n_chunks, a.batch), dim3(512), la_scores_lds(a.d, a.Wk, 2),
-                         st, a);
-  } else {
-    if (k_wide)
-      hipLaunchKernelGGL((layer_scores_kernel<1, LA_WMAX>), dim3(a.n_chunks, a.batch, 2), dim3(512),
-                         la_scores_lds(a.d, a.Wk, 1), st, a);
-    else
-      hipLaunchKernelGGL((layer_scores_kernel<1, 64>), dim3(a.n_chunks, a.batch, 2), dim3(512),
-                         la_scores_lds(a.d, a.Wk, 1), st, a);
-  }
+  hipLaunchKernelGGL(layer_scores_kernel, dim3(a.n_chunks, a.batch), dim3(64 * LA_SW), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(layer_stats_kernel, dim3(a.n_q_heads, a.batch), dim3(256), 0, st, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (v_wide)
-    hipLaunchKernelGGL(layer_values_kernel<LA_WMAX>, dim3(a.nv_chunks, 2, a.batch), dim3(512), 0, st, a);
+  if (la_prefetch_words(a.Wv) > 64)
+    hipLaunchKernelGGL(layer_values_kernel<LA_WMAX>, dim3(a.nv_chunks, 4, a.batch), dim3(512), 0, st, a);
   else
-    hipLaunchKernelGGL(layer_values_kernel<64>, dim3(a.nv_chunks, 2, a.batch), dim3(512), 0, st, a);
+    hipLaunchKernelGGL(layer_values_kernel<64>, dim3(a.nv_chunks, 4, a.batch), dim3(512), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(layer_combine_kernel, dim3(a.n_q_heads, a.batch, a.d / 64), dim3(256), 0, st, a);

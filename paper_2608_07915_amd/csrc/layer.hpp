@@ -70,23 +70,20 @@ struct LayerAttnArgs {
   int32_t batch, n_q_heads, n_kv_heads, d, Wk, Wv;
   float scale_log2;
   int32_t n_chunks, tiles_per_chunk;     // score pass: token chunks
-  int32_t nv_chunks, v_tiles_per_chunk;  // value pass: token chunks (x 2 head blocks)
+  int32_t nv_chunks, v_tiles_per_chunk;  // value pass: two score chunks each (x 2 head blocks)
   float* qt;      // [batch][Hq][d]: scale log2(e) q_h V_K[kv rows], 0 on dropped groups
-  float* ml;      // [batch][Hq][2]: softmax max and sum over all tokens
   uint16_t* qh;   // [batch][2][32][d] fp16: qt as high and low parts, kept groups in slot order
   float* qsum;    // [batch][Hq][16]: per group sums of qt
-  float* scores;  // [batch][Hq][n_tokens] (log2 domain)
-  float* stats;   // [batch][n_chunks][Hq][2]: chunk max, chunk sum of exp2(s - max)
-  float* part;    // [batch][nv_chunks][Hq][d + 16]: value sums per coefficient, zero-point sums per group
+  float* scores;  // [batch][tile][Hq][64] (log2 domain)
+  float* cmax;    // [batch][n_chunks][Hq]: chunk maxima of the scores
+  float* part;    // [batch][nv_chunks][Hq][d + 32]: value sums per coefficient, zero-point sums per group, weights' sum
   float* out;     // [batch][Hq][128]
 };
 
 }  // namespace spectra_dev
 
 namespace spectra {
-int32_t layer_attention_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk);
 size_t layer_attention_ws_floats(int32_t batch, int32_t n_q_heads, int32_t d, int64_t n_tokens);
 void layer_attention_ws_layout(spectra_dev::LayerAttnArgs& a, float* ws);
-size_t layer_scores_lds_bytes(int32_t d, int32_t Wk);
 hipError_t launch_layer_attention(const spectra_dev::LayerAttnArgs& a, hipStream_t st);
 }  // namespace spectra
