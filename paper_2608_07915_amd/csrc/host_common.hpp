@@ -7,6 +7,15 @@
 
 #include "spectra.h"
 
+// Row loops of the fit, compiled for wider vectors as well and chosen at load time. The
+// contraction of products and sums stays off there: all variants round alike.
+#if defined(__x86_64__) && defined(__clang__) && !defined(__HIP__)
+#pragma clang fp contract(off)
+#define SPECTRA_ROW_CLONES __attribute__((target_clones("avx512f", "avx2", "default")))
+#else
+#define SPECTRA_ROW_CLONES
+#endif
+
 namespace spectra {
 
 // Thread-local text of the last error; set by fail().

@@ -66,6 +66,29 @@ spectra_status check_params_gpu(const spectra_params& p) {
   return SPECTRA_OK;
 }
 
+// mean[j] = sum_i mu_i V_ij and var[j] = sum_i V_ij (C V)_ij, every sum in ascending i (and
+// k inside), taken as row updates over all j at once: as one dependent chain per j this was
+// 2 ms of a 128-wide fit's 4.5.
+SPECTRA_ROW_CLONES static void coefficient_moments(int d, const double* mu, const double* C, const double* V, double* Cv,
+                                                   float* mean, double* var) {
+  double* m = Cv;  // first as scratch
+  for (int j = 0; j < d; ++j) m[j] = 0.0;
+  for (int i = 0; i < d; ++i)
+    for (int j = 0; j < d; ++j) m[j] += mu[i] * V[(size_t)i * d + j];
+  for (int j = 0; j < d; ++j) mean[j] = (float)m[j];
+  for (int i = 0; i < d; ++i) {
+    double* row = Cv + (size_t)i * d;
+    for (int j = 0; j < d; ++j) row[j] = 0.0;
+    for (int k = 0; k < d; ++k) {
+      const double c = C[(size_t)i * d + k];
+      for (int j = 0; j < d; ++j) row[j] += c * V[(size_t)k * d + j];
+    }
+  }
+  for (int j = 0; j < d; ++j) var[j] = 0.0;
+  for (int i = 0; i < d; ++i)
+    for (int j = 0; j < d; ++j) var[j] += V[(size_t)i * d + j] * Cv[(size_t)i * d + j];
+}
+
 spectra_status fit_from_moments(const spectra_params& p, int64_t n_tokens, const double* gram,
                                 const double* colsum, float* basis, float* mean, double* var,
                                 uint8_t* bits, float* scale) {
@@ -93,20 +116,8 @@ spectra_status fit_from_moments(const spectra_params& p, int64_t n_tokens, const
     V32[i] = (double)basis[i];
   }
   // m = mu . V32 (coefficient-space mean), v_j = V32_j^T C V32_j (centered variance)
-  std::vector<double> Cv(d);
-  for (int j = 0; j < d; ++j) {
-    double m = 0.0;
-    for (int i = 0; i < d; ++i) m += mu[i] * V32[(size_t)i * d + j];
-    mean[j] = (float)m;
-    for (int i = 0; i < d; ++i) {
-      double s = 0.0;
-      for (int k = 0; k < d; ++k) s += C[(size_t)i * d + k] * V32[(size_t)k * d + j];
-      Cv[i] = s;
-    }
-    double vj = 0.0;
-    for (int i = 0; i < d; ++i) vj += V32[(size_t)i * d + j] * Cv[i];
-    var[j] = vj;
-  }
+  std::vector<double> Cv((size_t)d * d);
+  coefficient_moments(d, mu.data(), C.data(), V32.data(), Cv.data(), mean, var);
   if (scale) {
     // Eq. gsvd, square-root split: coordinate j of the orthonormal latent times
     // lambda_j^(-1/4) (lambda floored at lambda_0 2^-40); widths from the scaled variances
