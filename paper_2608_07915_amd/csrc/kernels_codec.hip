@@ -9,7 +9,9 @@
 // workgroup; each wave keeps the basis columns of one kept group in registers.
 //
 // Decode (Sec. 3.3, Mode A): x_hat = sum_G (z_G 1 + s_G q_G) V_G^T + m V^T, with the
-// q_G V_G^T contraction on MFMA (codes are exact small integers in bf16).
+// q_G V_G^T contraction on MFMA (codes are exact small integers in fp16, the basis enters as
+// two scaled fp16 parts).
+#include "code_operands.hpp"
 #include "device_common.hpp"
 #include "encode_dev.hpp"
 #include "kernels.hpp"
@@ -338,14 +340,35 @@ __global__ __launch_bounds__(256, 2) void encode_f32_kernel(EncodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Decode: wave w owns output channels 32w..32w+31 for every token of a super-tile.
+// Decode: a wavefront rebuilds all 128 channels of 64-token tiles (lane = token of a tile).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void decode_kernel(DecodeArgs a) {
-  // super-tile = two 64-token record tiles; records of W <= 32 words are double-buffered
-  // (the next super-tile is copied HBM -> LDS by global_load_lds while this one is
-  // decoded), wider ones go through one buffer
-  __shared__ __attribute__((aligned(16))) uint32_t rec[2 * 64 * 64];
-  __shared__ __attribute__((aligned(16))) float vsum_s[NG][D], bias_s[D];
+// The basis sits in LDS as two fp16 parts per kept group, scaled by the power of two that
+// brings the group's largest entry into [2^8, 2^9). A lane turns its own token's payload
+// words into all 32 codes of a group (centered fp16 integers); one swap of the wavefront's
+// halves per register makes the operands of both 32-token blocks of the tile, so no code
+// is unpacked twice and wavefronts exchange nothing:
+//   out[ch][t] = sum_slots s_t (V[ch] . q'_t)  +  (zero-point and mean terms),
+// the latter one product per tile, sum_slots (z_t + 2^(b-1) s_t) sum_j V[ch][j] + m V^T,
+// as bf16 parts (six cross terms per slot, three parts of m V^T against ones).
+// The codes are the row operand and column c of channel block b is channel 4c + b, so a
+// lane's four blocks are four neighbouring channels and every store of a wavefront is two
+// whole rows (with channels as rows, each store left 32-byte pieces of 32 rows: 192 us).
+// Every record word of the next tile is in flight before this tile's rows are stored (the
+// vector memory counter retires in order: a load behind 64 stores would wait for them).
+// Bound by the fp32 rows written: 537 MB for eight heads of 131k tokens, 106 us for stores
+// alone in this pattern. With 32 channels per wavefront, three bf16 parts and every code
+// unpacked by four wavefronts 176 us, now 128 us at 8x.
+constexpr int DC_NW = 8;         // wavefronts per workgroup
+constexpr int DC_VP = D + 8;     // fp16 per basis row (272 bytes: 16 rows on distinct banks)
+constexpr int DC_YP = 32 + 8;    // bf16 per row of group sums and m V^T
+__host__ __device__ constexpr int decode_lds_bytes() { return (2 * D * DC_VP + D * DC_YP) * 2; }
+
+__global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t dsm[];
+  uint16_t(*vl)[D][DC_VP] = reinterpret_cast<uint16_t(*)[D][DC_VP]>(dsm);            // [part][row][32 slot + place]
+  uint16_t(*yl)[DC_YP] = reinterpret_cast<uint16_t(*)[DC_YP]>(dsm + 2 * D * DC_VP * 2);  // [row][8 slot + element]
+  __shared__ float vmax[DC_NW][NG];
+  __shared__ __attribute__((aligned(16))) float scl[DC_NW][TILE];  // a slot's scales of each wavefront's tile
   const int s = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -353,145 +376,209 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(DecodeArgs a) {
   const Kept K = read_kept(a.bits + (int64_t)s * NG);
   const int W = a.W;
   if (!K.ok || K.used > W) return;  // width table inconsistent with the record: write nothing
-  const int64_t sbase = (int64_t)s * a.t_cap * W;
-  const int ch = 32 * wave + col;  // channel of this lane's basis operand row
-  const float* Vs = a.basis + (int64_t)s * D * D;
+  const int64_t first_tile = a.t0 >> 6, end = a.t0 + a.n;
+  const int64_t n_tiles = ((end - 1) >> 6) - first_tile + 1;
+  const int64_t step = (int64_t)gridDim.x * DC_NW;
+  int64_t tile = (int64_t)blockIdx.x * DC_NW + wave;
 
-  const int64_t first_tile = a.t0 >> 6;
-  const int64_t end = a.t0 + a.n;
-  const int64_t last_tile = (end - 1) >> 6;
-  const int64_t n_st = (last_tile - first_tile + 2) / 2;
-  const bool db = W <= 32;
-  // super-tile st into buffer b: its words are contiguous in HBM (tile-major), 16 bytes
-  // per lane and copy; lanes past the super-tile's last word re-read its last piece
-  // (their LDS slots are never read)
-  auto issue = [&](int64_t st, int b) {
-    const int64_t tile0 = first_tile + 2 * st;
-    const int ntile = (tile0 + 1 <= last_tile) ? 2 : 1;
-    const int np = ntile * 16 * W;  // 16-byte pieces
-    const uint32_t* src = a.packed + sbase + tile0 * (int64_t)(64 * W);
-    uint32_t* dst = rec + b * (64 * 64);
+  // this lane's token of a tile: payload words and metadata of every kept slot
+  const uint32_t* rec = a.packed + (int64_t)s * a.t_cap * W + first_tile * (int64_t)(TILE * W) + lane;
+  uint32_t words[NG][8], meta[NG];
+  auto load_slot = [&](int sl, int64_t tt) {
+    const uint32_t* src = rec + tt * (int64_t)(TILE * W);
+    const int b = K.bits[sl], pay = K.pay[sl];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int p0 = 256 * i + 64 * wave;
-      if (p0 < np) {
-        const int pc = p0 + lane < np ? p0 + lane : np - 1;
-        __builtin_amdgcn_global_load_lds(src + 4 * pc, dst + 4 * p0, 16, 0, 0);
-      }
-    }
+    for (int i = 0; i < 8; ++i)
+      if (i < b) words[sl][i] = src[(pay + i) * TILE];
+    meta[sl] = src[sl * TILE];
   };
-  int64_t st = blockIdx.x;
-  if (st >= n_st) return;
-  issue(st, 0);
+  if (tile < n_tiles) {
+#pragma unroll
+    for (int sl = 0; sl < NG; ++sl)
+      if (sl < K.n) load_slot(sl, tile);
+  }
 
-  // A operands: row = channel ch, K = in-group coefficients 16k + 8h + i.
-  bf16x8 Vb[NG][2][3];
+  // ---- basis to LDS: thread = (channel tid / 4, group tid % 4) ----
+  float exps[NG];  // per slot: 2^-e of its scale 2^e
+  {
+    const int ch = tid >> 2, g = tid & 3;
+    const int row = 32 * (ch & 3) + (ch >> 2);  // column c of block b is channel 4c + b
+    const float* vr = a.basis + (int64_t)s * D * D + (int64_t)ch * D + G * g;
+    const float* mr = a.mean + (int64_t)s * D + G * g;
+    float v[32], m[32];
 #pragma unroll
-  for (int sl = 0; sl < NG; ++sl) {
-    if (sl < K.n) {
-      const float* vr = Vs + (int64_t)ch * D + G * K.grp[sl];
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(&v[4 * i]) = *reinterpret_cast<const f32x4*>(vr + 4 * i);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        uint32_t p0[8], p1[8], p2[8];
+    for (int i = 0; i < 32; ++i) m[i] = mr[i];
+    float sum = 0.0f, bias = 0.0f, big = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) split3(vr[16 * k + 8 * h + i], p0[i], p1[i], p2[i]);
-        Vb[sl][k][0] = as_bf16x8(u32x4{pack2(p0[0], p0[1]), pack2(p0[2], p0[3]), pack2(p0[4], p0[5]), pack2(p0[6], p0[7])});
-        Vb[sl][k][1] = as_bf16x8(u32x4{pack2(p1[0], p1[1]), pack2(p1[2], p1[3]), pack2(p1[4], p1[5]), pack2(p1[6], p1[7])});
-        Vb[sl][k][2] = as_bf16x8(u32x4{pack2(p2[0], p2[1]), pack2(p2[2], p2[3]), pack2(p2[4], p2[5]), pack2(p2[6], p2[7])});
-      }
-      if (h == 0) {
-        float acc = 0.0f;
-        for (int j = 0; j < G; ++j) acc += vr[j];
-        vsum_s[sl][ch] = acc;
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) Vb[sl][k][p] = bf16x8{};
+    for (int i = 0; i < 32; ++i) {
+      sum += v[i];
+      bias = __builtin_fmaf(m[i], v[i], bias);
+      big = __builtin_fmaxf(big, __builtin_fabsf(v[i]));
     }
+    bias += __shfl_xor(bias, 1);
+    bias += __shfl_xor(bias, 2);
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
+    if (lane < NG) vmax[wave][lane] = big;
+    int slot = -1;  // kept slot of group g
+#pragma unroll
+    for (int sl = 0; sl < NG; ++sl) slot = (sl < K.n && K.grp[sl] == g) ? sl : slot;
+    __syncthreads();
+    int myexp = 0;
+#pragma unroll
+    for (int sl = 0; sl < NG; ++sl) {
+      float mx = 0.0f;
+#pragma unroll
+      for (int w = 0; w < DC_NW; ++w) mx = __builtin_fmaxf(mx, vmax[w][K.grp[sl]]);
+      const int e = __builtin_amdgcn_readfirstlane(9 - scale_exponent(mx));
+      exps[sl] = __builtin_ldexpf(1.0f, -e);
+      myexp = sl == slot ? e : myexp;
+    }
+    const float sc = __builtin_ldexpf(1.0f, myexp);
+    if (slot >= 0) {
+      // coefficients c and c + 16 are neighbours in K: place 2 (c & 15) + (c >> 4)
+      uint32_t hi[16], lo[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) split2_f16(v[i], v[16 + i], sc, hi[i], lo[i]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        *reinterpret_cast<u32x4*>(&vl[0][row][G * slot + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
+        *reinterpret_cast<u32x4*>(&vl[1][row][G * slot + 8 * q]) = u32x4{lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]};
+      }
+    }
+    // row of the zero-point product: slot k has elements 8k .. 8k + 5 = group-sum parts
+    // 0 0 1 0 1 2 (against z parts 0 1 0 2 1 0); elements 6, 7, 14 hold the parts of m V^T
+    // (against ones); threads of dropped groups fill the slots past the kept ones with zeros
+    uint32_t p0, p1, p2, b0, b1, b2;
+    split3(slot >= 0 ? sum : 0.0f, p0, p1, p2);
+    split3(bias, b0, b1, b2);
+    int rank = 0;  // dropped group: its place among the slots past the kept ones
+#pragma unroll
+    for (int gg = 0; gg < NG; ++gg) {
+      bool kept = false;
+#pragma unroll
+      for (int sl = 0; sl < NG; ++sl) kept = kept || (sl < K.n && K.grp[sl] == gg);
+      rank += (!kept && gg < g) ? 1 : 0;
+    }
+    const int ys = slot >= 0 ? slot : K.n + rank;
+    const uint32_t tail = ys == 0 ? pack2(b0, b1) : ys == 1 ? pack2(b2, 0u) : 0u;
+    *reinterpret_cast<u32x4*>(&yl[row][8 * ys]) = u32x4{pack2(p0, p0), pack2(p1, p0), pack2(p1, p2), tail};
   }
-  if (h == 0) {
-    const float* ms = a.mean + (int64_t)s * D;
-    const float* vr = Vs + (int64_t)ch * D;
-    float bias = 0.0f;
-    for (int j = 0; j < D; ++j) bias += ms[j] * vr[j];
-    bias_s[ch] = bias;
-  }
-  wait_vmcnt<0>();  // this wave's copies of the first super-tile (and the operand loads) done
-  __syncthreads();  // ... every wave's; vsum and bias visible
+  __syncthreads();
 
-  int buf = 0;
-  for (;;) {
-    const int64_t st_next = st + gridDim.x;
-    const bool more = st_next < n_st;
-    if (db && more) issue(st_next, buf ^ 1);
-    const int64_t tile0 = first_tile + 2 * st;
-    const int ntile = (tile0 + 1 <= last_tile) ? 2 : 1;
-    const bool full = ntile == 2 && (tile0 << 6) >= a.t0 && (tile0 << 6) + 128 <= end;
-    const uint32_t* rb = rec + buf * (64 * 64);
-    for (int beta = 0; beta < 2 * ntile; ++beta) {
-      const int row = 32 * beta + col;  // token of this lane's B-operand column
-      const uint32_t* rtok = rb + (row >> 6) * 64 * W + (row & 63);
-      f32x16 out = {};
+  uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
+  asm volatile("" : "+v"(magic));
+  for (; tile < n_tiles; tile += step) {
+    const int64_t next = tile + step < n_tiles ? tile + step : tile;  // past the last tile: its words again
+    f32x16 out[2][4];  // [32-token block][32-channel block]
+    // zero-point and mean terms: lane = token packs its slots' elements, the half swap makes
+    // the operands of both blocks (slots 0 and 1 in K step 0, 2 and 3 in K step 1)
+    uint32_t ze[NG][4];
 #pragma unroll
-      for (int sl = 0; sl < NG; ++sl) {
-        if (sl < K.n) {
-          f32x16 acc = {};
-          with_bits(K.bits[sl], [&](auto bc) {
-            constexpr int B = decltype(bc)::value;
-            const int pay = K.pay[sl];
-            auto word = [&](int i) { return rtok[(pay + i) * 64]; };
+    for (int sl = 0; sl < NG; ++sl) {
+      uint32_t z0 = 0u, z1 = 0u, z2 = 0u;
+      if (sl < K.n) {
+        const float mid = (float)(1 << (K.bits[sl] - 1));
+        split3(__builtin_fmaf(h2f(meta[sl]), mid, h2f(meta[sl] >> 16)), z0, z1, z2);
+      }
+      ze[sl][0] = pack2(z0, z1);
+      ze[sl][1] = pack2(z0, z2);
+      ze[sl][2] = pack2(z1, z0);
+      ze[sl][3] = sl == 0 ? 0x3F803F80u : sl == 1 ? 0x00003F80u : 0u;
+    }
+    {
+      bf16x8 zop[2][2];  // [K step][block]
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-              uint32_t cd[8];
-              extract8<B>(word, 16 * k + 8 * h, cd);
-              const bf16x8 C = as_bf16x8(u32x4{int_to_bf16_pair(cd[0], cd[1]), int_to_bf16_pair(cd[2], cd[3]),
-                                               int_to_bf16_pair(cd[4], cd[5]), int_to_bf16_pair(cd[6], cd[7])});
-              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Vb[sl][k][0], C, acc, 0, 0, 0);
-              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Vb[sl][k][1], C, acc, 0, 0, 0);
-              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Vb[sl][k][2], C, acc, 0, 0, 0);
+      for (int ks = 0; ks < 2; ++ks) {
+        u32x4 za, zb;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const auto r = __builtin_amdgcn_permlane32_swap(ze[2 * ks][i], ze[2 * ks + 1][i], false, false);
+          za[i] = r[0];
+          zb[i] = r[1];
+        }
+        zop[ks][0] = as_bf16x8(za);
+        zop[ks][1] = as_bf16x8(zb);
+      }
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) {
+        const bf16x8 y0 = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[32 * cb + col][8 * h]));
+        const bf16x8 y1 = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[32 * cb + col][16 + 8 * h]));
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+          f32x16 o = {};
+          if (K.n > 2) o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zop[1][tb], y1, o, 0, 0, 0);
+          out[tb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zop[0][tb], y0, o, 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int sl = 0; sl < NG; ++sl) {
+      if (sl < K.n) {
+        f16x8 cod[2][2];  // [block][K step]
+        with_bits(K.bits[sl], [&](auto bc) {
+          constexpr int B = decltype(bc)::value;
+          uint32_t Z[8];
+          join_halves<B>(words[sl], Z);
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            const u32x4 x = __builtin_bit_cast(u32x4, codes_f16<B>(Z, ks, magic));
+            const u32x4 y = __builtin_bit_cast(u32x4, codes_f16<B>(Z, ks + 2, magic));
+            u32x4 ca, cb;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const auto r = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
+              ca[i] = r[0];
+              cb[i] = r[1];
             }
-          });
-          // acc[4q + r]: channel 32 wave + 8q + 4h + r, token row (the lane's column)
-          const uint32_t m = rtok[sl * 64];
-          const float sc = h2f(m), zc = h2f(m >> 16);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 v4 = *reinterpret_cast<const f32x4*>(&vsum_s[sl][32 * wave + 8 * q + 4 * h]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) out[4 * q + r] = __builtin_fmaf(sc, acc[4 * q + r], __builtin_fmaf(zc, v4[r], out[4 * q + r]));
+            cod[0][ks] = __builtin_bit_cast(f16x8, ca);
+            cod[1][ks] = __builtin_bit_cast(f16x8, cb);
           }
-        }
-      }
-      const int64_t t = (tile0 << 6) + row;
-      float* o = a.out + ((int64_t)s * a.n + (t - a.t0)) * D + 32 * wave + 4 * h;
-      if (full || (t >= a.t0 && t < end)) {
+        });
+        // each token's scale, back from LDS for the rows of this lane's sums
+        scl[wave][lane] = h2f(meta[sl]) * exps[sl];
+        f32x4 st[2][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias_s[32 * wave + 8 * q + 4 * h]);
-          *reinterpret_cast<f32x4*>(o + 8 * q) =
-              f32x4{out[4 * q] + b4[0], out[4 * q + 1] + b4[1], out[4 * q + 2] + b4[2], out[4 * q + 3] + b4[3]};
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) st[tb][q] = *reinterpret_cast<const f32x4*>(&scl[wave][32 * tb + 8 * q + 4 * h]);
+        load_slot(sl, next);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+          f32x16 g[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+              const f16x8 av = *reinterpret_cast<const f16x8*>(&vl[p][32 * cb + col][G * sl + 16 * h + 8 * ks]);
+#pragma unroll
+              for (int tb = 0; tb < 2; ++tb) g[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cod[tb][ks], av, g[tb], 0, 0, 0);
+            }
+#pragma unroll
+          for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) out[tb][cb][i] = __builtin_fmaf(st[tb][i >> 2][i & 3], g[tb][i], out[tb][cb][i]);
         }
+        // the sums stay here (not sunk past the next slots with all products alive)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) asm volatile("" : "+v"(out[0][cb]), "+v"(out[1][cb]));
       }
     }
-    if (!more) break;
-    if (db) {
-      // this wave's copies of the next super-tile were issued before the 16 stores of a
-      // full super-tile (vector memory operations complete in issue order)
-      if (full)
-        wait_vmcnt<16>();
-      else
-        wait_vmcnt<0>();
-      __syncthreads();  // every wave's copies landed; every wave is done with rec[buf]
-      buf ^= 1;
-    } else {
-      __syncthreads();  // every wave is done with the buffer
-      issue(st_next, 0);
-      wait_vmcnt<0>();
-      __syncthreads();
-    }
-    st = st_next;
+    // lane (h, col): channels 4 col .. 4 col + 3 of tokens 8q + 4h + r: every store of the
+    // wavefront is two whole 512-byte rows
+    const int64_t t0 = ((first_tile + tile) << 6) + 4 * h;
+    float* o = a.out + ((int64_t)s * a.n + (t0 - a.t0)) * D + 4 * col;
+    const bool whole = ((first_tile + tile) << 6) >= a.t0 && ((first_tile + tile) << 6) + TILE <= end;
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = 32 * tb + 8 * (i >> 2) + (i & 3);
+        if (whole || (t0 + r >= a.t0 && t0 + r < end))
+          *reinterpret_cast<f32x4*>(o + r * D) = f32x4{out[tb][0][i], out[tb][1][i], out[tb][2][i], out[tb][3][i]};
+      }
   }
 }
 
@@ -669,13 +756,12 @@ hipError_t launch_encode(const EncodeArgs& a, bool f32_input, hipStream_t st) {
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
   const int64_t first_tile = a.t0 >> 6, last_tile = (a.t0 + a.n - 1) >> 6;
-  const int64_t n_st = (last_tile - first_tile + 2) / 2;
-  // one round of workgroups (two per CU): the basis operands are set up once per
-  // workgroup, and each workgroup streams many super-tiles
-  int64_t per_stream = (512 + a.n_streams - 1) / a.n_streams;
-  if (per_stream > n_st) per_stream = n_st;
-  if (per_stream < 1) per_stream = 1;
-  hipLaunchKernelGGL(decode_kernel, dim3((unsigned)per_stream, (unsigned)a.n_streams), dim3(256), 0, st, a);
+  const int64_t n_tiles = last_tile - first_tile + 1;
+  // one round of workgroups (one per CU: LDS and registers): the basis is split once per
+  // workgroup, and each wavefront streams many tiles
+  int64_t per_stream = (256 + a.n_streams - 1) / a.n_streams;
+  if (per_stream > (n_tiles + DC_NW - 1) / DC_NW) per_stream = (n_tiles + DC_NW - 1) / DC_NW;
+  hipLaunchKernelGGL(decode_kernel, dim3((unsigned)per_stream, (unsigned)a.n_streams), dim3(64 * DC_NW), decode_lds_bytes(), st, a);
   return hipGetLastError();
 }
 

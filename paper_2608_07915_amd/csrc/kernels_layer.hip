@@ -336,9 +336,10 @@ __global__ __launch_bounds__(512, 4) void layer_encode_kernel(LayerEncodeArgs a)
 // against 64 bits went down (2.9e-7 -> 2.3e-7). The zero-point terms (z_t + 2^(b-1) s_t)
 // sum_j V[ch][j] of all groups are one product over the slots per range (three bf16 parts
 // each side), and m V^T is added last.
-// A 131k-token 1024-wide layer at 8x: 1830 -> 495 us. Matrix cores busy 42%, vector ALU
-// 40%, the rest is the store bursts at a range's end (90 us of it with the stores removed)
-// and waiting inside a step. What was tried and is slower: a workgroup per range (720 us:
+// The codes are the row operand and column c of channel block b is channel 4c + b, so every
+// store of a wavefront is two whole 512-byte row pieces.
+// A 131k-token 1024-wide layer at 8x: 1860 -> 483 us. Matrix cores busy 45%, vector ALU
+// 44%, the rest is the store bursts at a range's end and waiting inside a step. What was tried and is slower: a workgroup per range (720 us:
 // its prologue and epilogue overlap nothing), 64 tokens x 64 channels per wavefront (560
 // us, every code unpacked twice), 64 x 128 (490 to 520 us, spills), four wavefronts
 // with four times the registers (770 us).
@@ -346,15 +347,10 @@ constexpr int LD_CH = 128;     // channels per workgroup
 constexpr int LD_NW = 8;       // wavefronts per workgroup
 constexpr int LD_TOK = 32 * LD_NW;  // tokens per range
 constexpr int LD_P = LG + 8;   // fp16 per LDS row (144 bytes: 16 rows on distinct banks)
+constexpr int LD_RB = 33;      // rows from one 32-channel block to the next (the four blocks' rows of a write on distinct banks)
 constexpr int LD_YP = 24;      // bf16 per row of the group sums (16 slots + pad)
 constexpr int LD_ZP = 20;      // floats per row of the zero points (16 slots + pad)
 
-// The exponent e with v in [2^(e-1), 2^e), limited so that 2^(9 - e) and its inverse are normal.
-__device__ __forceinline__ int scale_exponent(float v) {
-  int e = 0;
-  if (v > 0.0f && v < __builtin_inff()) (void)__builtin_frexpf(v, &e);
-  return e < -100 ? -100 : (e > 100 ? 100 : e);
-}
 __device__ __forceinline__ void split_row3(const float (&x)[8], bf16x8 (&p)[3]) {
   uint32_t p0[8], p1[8], p2[8];
 #pragma unroll
@@ -368,9 +364,10 @@ template <bool SCALED>
 __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecodeArgs a) {
   constexpr int NT = 64 * LD_NW;
   static_assert(NT == 4 * LD_CH, "a thread stages a quarter of a channel's 64 coefficients");
-  __shared__ __attribute__((aligned(16))) uint16_t vl[2][2][LD_CH][LD_P];  // [buffer][part][channel][place]
-  __shared__ __attribute__((aligned(16))) uint16_t yl[3][LD_CH][LD_YP];    // [part][channel][slot]: group sums
+  __shared__ __attribute__((aligned(16))) uint16_t vl[2][2][4 * LD_RB][LD_P];  // [buffer][part][row][place]
+  __shared__ __attribute__((aligned(16))) uint16_t yl[3][4 * LD_RB][LD_YP];    // [part][row][slot]: group sums
   __shared__ __attribute__((aligned(16))) float zl[LD_TOK][LD_ZP];         // [token][slot]: centered zero points
+  __shared__ __attribute__((aligned(16))) float scl[LD_TOK];               // scales of the slot at hand
   __shared__ __attribute__((aligned(16))) float bias[LD_CH];
   __shared__ __attribute__((aligned(16))) float mean[1024];
   __shared__ float vmax[16][LD_NW];
@@ -389,7 +386,7 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
   const float* Vs = a.basis + (int64_t)s * d * d;
   if (wave == 0) layer_table(a.bits + (int64_t)s * ng, ng, lane, tab);
   for (int i = tid; i < d; i += NT) mean[i] = a.mean[(int64_t)s * d + i];
-  for (int i = tid; i < 3 * LD_CH * LD_YP / 2; i += NT) reinterpret_cast<uint32_t*>(yl)[i] = 0u;  // slots past the kept ones
+  for (int i = tid; i < 3 * 4 * LD_RB * LD_YP / 2; i += NT) reinterpret_cast<uint32_t*>(yl)[i] = 0u;  // slots past the kept ones
   for (int i = tid; i < LD_TOK * LD_ZP; i += NT) reinterpret_cast<float*>(zl)[i] = 0.0f;
   __syncthreads();
   if (!tab.ok || tab.used > a.W) return;  // width table inconsistent with the record: write nothing
@@ -397,10 +394,11 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
 
   // staging share: channel row tid >> 2, group coefficients c0 .. c0 + 7 and c0 + 16 ..
   // c0 + 23, which are 16 consecutive places of the operand row
-  const int row = tid >> 2, sub = tid & 3, c0 = 32 * (sub >> 1) + 8 * (sub & 1);
+  const int ch = tid >> 2, sub = tid & 3, c0 = 32 * (sub >> 1) + 8 * (sub & 1);
+  const int row = LD_RB * (ch & 3) + (ch >> 2);  // column c of 32-channel block b is channel 4c + b
   float v[16];
   auto load_v = [&](int g, float (&x)[16]) {
-    const float* src = Vs + (int64_t)(ch0 + row) * d + LG * g + c0;
+    const float* src = Vs + (int64_t)(ch0 + ch) * d + LG * g + c0;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       *reinterpret_cast<f32x4*>(&x[4 * q]) = *reinterpret_cast<const f32x4*>(src + 16 * (q >> 1) + 4 * (q & 1));
@@ -444,7 +442,7 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
     }
     bsum += __shfl_xor(bsum, 1);
     bsum += __shfl_xor(bsum, 2);
-    if (sub == 0) bias[row] = bsum;
+    if (sub == 0) bias[ch] = bsum;
   }
   __syncthreads();
   if (tid < n_kept) {
@@ -467,11 +465,7 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
     uint32_t hi[8], lo[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {  // coefficients c0 + i and c0 + 16 + i are neighbours in K
-      const f32x2 x = f32x2{v[i] * sc, v[8 + i] * sc};
-      const f16x2 xh = __builtin_convertvector(x, f16x2);
-      const f16x2 xl = __builtin_convertvector(f32x2{x[0] - (float)xh[0], x[1] - (float)xh[1]}, f16x2);
-      hi[i] = __builtin_bit_cast(uint32_t, xh);
-      lo[i] = __builtin_bit_cast(uint32_t, xl);
+      split2_f16(v[i], v[8 + i], sc, hi[i], lo[i]);
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -505,9 +499,9 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
   };
   uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
   asm volatile("" : "+v"(magic));
-  // operands, scale and centered zero point of the slot whose words are held
+  // operands and centered zero point of the slot whose words are held (its scale is in LDS)
   f16x8 cod[4];
-  float st = 0.0f, zc = 0.0f;
+  float zc = 0.0f;
   int u_slot = 0;
   auto unpack = [&]() {
     const int bw = of_slot(slot_b, u_slot);
@@ -519,26 +513,29 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
       for (int k = 0; k < 4; ++k) cod[k] = codes_f16<B>(Z, k, magic);
     });
     const float sv = h2f(meta);
-    st = sv * __builtin_ldexpf(1.0f, -of_slot(slot_exp, u_slot));
+    scl[tw + col] = sv * __builtin_ldexpf(1.0f, -of_slot(slot_exp, u_slot));
     zc = __builtin_fmaf(sv, (float)(1 << (bw - 1)), h2f(meta >> 16));
     u_slot = u_slot + 1 < n_kept ? u_slot + 1 : 0;
   };
   f32x16 out[4];  // 32-channel blocks
   auto multiply = [&](int slot, int buf) {
     zl[tw + col][slot] = zc;
+    f32x4 sr[4];  // scales of the rows of this lane's sums
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sr[q] = *reinterpret_cast<const f32x4*>(&scl[tw + 8 * q + 4 * h]);
     // operands are read two K steps ahead and a channel block's sums are added while the
     // next block's products run
     constexpr int AHEAD = 2;
     f16x8 ah[AHEAD + 1], al[AHEAD + 1];
     f32x16 g[2];
     auto read_op = [&](int t) {
-      const uint16_t* src = &vl[buf][0][32 * (t >> 2) + col][32 * h + 8 * (t & 3)];
+      const uint16_t* src = &vl[buf][0][LD_RB * (t >> 2) + col][32 * h + 8 * (t & 3)];
       ah[t % (AHEAD + 1)] = *reinterpret_cast<const f16x8*>(src);
-      al[t % (AHEAD + 1)] = *reinterpret_cast<const f16x8*>(src + LD_CH * LD_P);
+      al[t % (AHEAD + 1)] = *reinterpret_cast<const f16x8*>(src + 4 * LD_RB * LD_P);
     };
     auto add_block = [&](int cb) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) out[cb][i] = __builtin_fmaf(st, g[cb & 1][i], out[cb][i]);
+      for (int i = 0; i < 16; ++i) out[cb][i] = __builtin_fmaf(sr[i >> 2][i & 3], g[cb & 1][i], out[cb][i]);
     };
 #pragma unroll
     for (int t = 0; t < AHEAD; ++t) read_op(t);
@@ -547,12 +544,12 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
       const int cb = t >> 2, k = t & 3;
       if (t + AHEAD < 16) read_op(t + AHEAD);
       if (k == 0) g[cb & 1] = f32x16{};
-      g[cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[t % (AHEAD + 1)], cod[k], g[cb & 1], 0, 0, 0);
-      g[cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[t % (AHEAD + 1)], cod[k], g[cb & 1], 0, 0, 0);
+      g[cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cod[k], ah[t % (AHEAD + 1)], g[cb & 1], 0, 0, 0);
+      g[cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cod[k], al[t % (AHEAD + 1)], g[cb & 1], 0, 0, 0);
       if (k == 3 && cb > 0) add_block(cb - 1);
     }
     add_block(3);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * AHEAD, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 4 + 2 * AHEAD, 0);
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
       if (t + AHEAD < 16) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
@@ -609,31 +606,32 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
     *reinterpret_cast<f32x4*>(&z[4]) = *reinterpret_cast<const f32x4*>(&zl[tw + col][8 * h + 4]);
     bf16x8 zp[3];
     split_row3(z, zp);
-    const int64_t i = range * LD_TOK + tw + col;
-    float* o = a.out + ((int64_t)s * a.n + i) * d + ch0 + 4 * h;
+    f32x16 y[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
       bf16x8 yp[3];
 #pragma unroll
-      for (int p = 0; p < 3; ++p) yp[p] = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[p][32 * cb + col][8 * h]));
-      f32x16 y = {};
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[0], zp[2], y, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[2], zp[0], y, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[1], zp[1], y, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[0], zp[1], y, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[1], zp[0], y, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yp[0], zp[0], y, 0, 0, 0);
-      // lane (h, col): rows 8q + 4h + r = channels, column col = token
-      if (i < a.n) {
+      for (int p = 0; p < 3; ++p) yp[p] = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[p][LD_RB * cb + col][8 * h]));
+      y[cb] = f32x16{};
+      y[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zp[2], yp[0], y[cb], 0, 0, 0);
+      y[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zp[0], yp[2], y[cb], 0, 0, 0);
+      y[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zp[1], yp[1], y[cb], 0, 0, 0);
+      y[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zp[1], yp[0], y[cb], 0, 0, 0);
+      y[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zp[0], yp[1], y[cb], 0, 0, 0);
+      y[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zp[0], yp[0], y[cb], 0, 0, 0);
+    }
+    // lane (h, col): channels 4 col .. 4 col + 3 of tokens 8q + 4h + r: a store of the
+    // wavefront is two whole 512-byte row pieces
+    const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias[4 * col]);
+    const int64_t i0 = range * LD_TOK + tw + 4 * h;
+    float* o = a.out + ((int64_t)s * a.n + i0) * d + ch0 + 4 * col;
+    const bool whole = range * LD_TOK + tw + 32 <= a.n;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias[32 * cb + 8 * q + 4 * h]);
-          f32x4 r;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) r[j] = (out[cb][4 * q + j] + y[4 * q + j]) + b4[j];
-          *reinterpret_cast<f32x4*>(o + 32 * cb + 8 * q) = r;
-        }
-      }
+    for (int i = 0; i < 16; ++i) {
+      const int r = 8 * (i >> 2) + (i & 3);
+      if (whole || i0 + r < a.n)
+        *reinterpret_cast<f32x4*>(o + (int64_t)r * d) =
+            f32x4{(out[0][i] + y[0][i]) + b4[0], (out[1][i] + y[1][i]) + b4[1], (out[2][i] + y[2][i]) + b4[2], (out[3][i] + y[3][i]) + b4[3]};
     }
   }
 }

@@ -1,0 +1,40 @@
+"""Per-head reconstruction at the edges of its tiles: every code width 1..8 in every slot, one
+to four kept groups, windows around the 64-token tiles, bases far from unit scale, against
+the oracle's fp64 decode of the same records (stale random words around them).
+
+The bar is that of the other decode tests (1e-6 relative L2): fp32 sums over at most 128
+coefficients of entries split with 2^-22 relative error."""
+import numpy as np
+import pytest
+
+import paper_2608_07915_amd as S
+from gpu_parity import rel_l2
+from layer_records import make_layer_cache
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+CASES = [
+    # widths of the four groups, tokens, first slot, streams, basis scale
+    ([8, 7, 6, 5], 63, 0, 2, 1.0),
+    ([4, 3, 2, 1], 65, 1, 2, 1.0),
+    ([1, 2, 3, 4], 129, 63, 1, 2.0 ** 30),
+    ([5, 6, 7, 8], 64, 64, 1, 2.0 ** -30),
+    ([0, 0, 0, 3], 1, 37, 3, 1.0),
+    ([0, 7, 0, 5], 1000, 5, 2, 1.0),
+    ([2, 0, 0, 0], 300, 0, 40, 1.0),
+    ([0, 0, 0, 0], 70, 2, 1, 1.0),
+    ([8, 8, 8, 8], 5000, 31, 1, 1.0),
+]
+
+
+@pytest.mark.parametrize("widths,T,t0,n,scale", CASES)
+def test_decode_edges(widths, T, t0, n, scale):
+    rng = np.random.default_rng([T, t0, n])
+    codec, packed, t_cap, want = make_layer_cache(rng, 128, widths, T, t0, n, scale, g=32)
+    got = S.spectra_decode(codec, packed, t_cap, t0, T).cpu().numpy()
+    for s in range(n):
+        assert rel_l2(got[s], want[s]) <= 1e-6
