@@ -60,4 +60,100 @@ __device__ __forceinline__ void split2_f16(float x0, float x1, float sc, uint32_
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[0] - (float)xh[0], x[1] - (float)xh[1]}, f16x2));
 }
 
+// ---------------------------------------------------------------------------
+// Basis of one KV head in LDS for a workgroup of eight wavefronts: row row_of(ch) of vl
+// holds channel ch's entries of the kept groups as two fp16 parts, group slot sl scaled by
+// the power of two that brings its largest entry into [2^8, 2^9) (exps[sl] is the inverse),
+// coefficient c of a group at place 2 (c & 15) + (c >> 4). The same row of yl is the other
+// operand of one product (K = 32, bf16) that gives a token's zero-point and mean terms,
+// sum_sl zc_sl sum_j V[ch][j] + (m V^T)[ch]: slot sl has elements 8 sl .. 8 sl + 5 = parts 0 0 1
+// 0 1 2 of the group's sum, against parts 0 1 0 2 1 0 of zc (zero_elements); elements 6,
+// 7 and 14 hold the parts of m V^T, against ones. The caller synchronises afterwards.
+// ---------------------------------------------------------------------------
+constexpr int HB_NW = 8;         // wavefronts of the workgroup: a thread per (channel, group)
+constexpr int HB_VP = D + 8;     // fp16 per basis row (272 bytes: 16 rows on distinct banks)
+constexpr int HB_YP = 32 + 8;    // bf16 per row of group sums and m V^T
+__host__ __device__ constexpr int hb_lds_bytes() { return (2 * D * HB_VP + D * HB_YP) * 2; }
+
+template <typename RowFn>
+__device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis, const float* __restrict__ mean, const Kept& K,
+                                                 int tid, uint16_t (*vl)[D][HB_VP], uint16_t (*yl)[HB_YP],
+                                                 float (*vmax)[NG], float (&exps)[NG], RowFn&& row_of) {
+  const int wave = tid >> 6, lane = tid & 63;
+  const int ch = tid >> 2, g = tid & 3;
+  const int row = row_of(ch);
+  const float* vr = basis + (int64_t)ch * D + G * g;
+  const float* mr = mean + G * g;
+  float v[32], m[32];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(&v[4 * i]) = *reinterpret_cast<const f32x4*>(vr + 4 * i);
+#pragma unroll
+  for (int i = 0; i < 32; ++i) m[i] = mr[i];
+  float sum = 0.0f, bias = 0.0f, big = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    sum += v[i];
+    bias = __builtin_fmaf(m[i], v[i], bias);
+    big = __builtin_fmaxf(big, __builtin_fabsf(v[i]));
+  }
+  bias += __shfl_xor(bias, 1);
+  bias += __shfl_xor(bias, 2);
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
+  if (lane < NG) vmax[wave][lane] = big;
+  int slot = -1;  // kept slot of group g
+#pragma unroll
+  for (int sl = 0; sl < NG; ++sl) slot = (sl < K.n && K.grp[sl] == g) ? sl : slot;
+  __syncthreads();
+  int myexp = 0;
+#pragma unroll
+  for (int sl = 0; sl < NG; ++sl) {
+    float mx = 0.0f;
+#pragma unroll
+    for (int w = 0; w < HB_NW; ++w) mx = __builtin_fmaxf(mx, vmax[w][K.grp[sl]]);
+    const int e = __builtin_amdgcn_readfirstlane(9 - scale_exponent(mx));
+    exps[sl] = __builtin_ldexpf(1.0f, -e);
+    myexp = sl == slot ? e : myexp;
+  }
+  const float sc = __builtin_ldexpf(1.0f, myexp);
+  if (slot >= 0) {
+    // coefficients c and c + 16 are neighbours in K: place 2 (c & 15) + (c >> 4)
+    uint32_t hi[16], lo[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) split2_f16(v[i], v[16 + i], sc, hi[i], lo[i]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      *reinterpret_cast<u32x4*>(&vl[0][row][G * slot + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
+      *reinterpret_cast<u32x4*>(&vl[1][row][G * slot + 8 * q]) = u32x4{lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]};
+    }
+  }
+  // row of the zero-point product: slot k has elements 8k .. 8k + 5 = group-sum parts
+  // 0 0 1 0 1 2 (against z parts 0 1 0 2 1 0); elements 6, 7, 14 hold the parts of m V^T
+  // (against ones); threads of dropped groups fill the slots past the kept ones with zeros
+  uint32_t p0, p1, p2, b0, b1, b2;
+  split3(slot >= 0 ? sum : 0.0f, p0, p1, p2);
+  split3(bias, b0, b1, b2);
+  int rank = 0;  // dropped group: its place among the slots past the kept ones
+#pragma unroll
+  for (int gg = 0; gg < NG; ++gg) {
+    bool kept = false;
+#pragma unroll
+    for (int sl = 0; sl < NG; ++sl) kept = kept || (sl < K.n && K.grp[sl] == gg);
+    rank += (!kept && gg < g) ? 1 : 0;
+  }
+  const int ys = slot >= 0 ? slot : K.n + rank;
+  const uint32_t tail = ys == 0 ? pack2(b0, b1) : ys == 1 ? pack2(b2, 0u) : 0u;
+  *reinterpret_cast<u32x4*>(&yl[row][8 * ys]) = u32x4{pack2(p0, p0), pack2(p1, p0), pack2(p1, p2), tail};
+}
+
+// The z side of that product for slot sl (< NG) of a token with metadata word m and width b
+// (0: no such slot): the centered zero point zc = z + 2^(b-1) s in three bf16 parts.
+__device__ __forceinline__ u32x4 zero_elements(uint32_t m, int b, uint32_t tail) {
+  uint32_t z0 = 0u, z1 = 0u, z2 = 0u;
+  if (b > 0) split3(__builtin_fmaf(h2f(m), __builtin_ldexpf(0.5f, b), h2f(m >> 16)), z0, z1, z2);
+  return u32x4{pack2(z0, z1), pack2(z0, z2), pack2(z1, z0), tail};
+}
+// The ones against m V^T: slot 0 has two of its parts, slot 1 the third.
+__device__ __forceinline__ uint32_t zero_tail(int sl) { return sl == 0 ? 0x3F803F80u : sl == 1 ? 0x00003F80u : 0u; }
+
 }  // namespace spectra_dev

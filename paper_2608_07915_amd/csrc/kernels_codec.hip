@@ -358,15 +358,13 @@ __global__ __launch_bounds__(256, 2) void encode_f32_kernel(EncodeArgs a) {
 // Bound by the fp32 rows written: 537 MB for eight heads of 131k tokens, 106 us for stores
 // alone in this pattern. With 32 channels per wavefront, three bf16 parts and every code
 // unpacked by four wavefronts 176 us, now 128 us at 8x.
-constexpr int DC_NW = 8;         // wavefronts per workgroup
-constexpr int DC_VP = D + 8;     // fp16 per basis row (272 bytes: 16 rows on distinct banks)
-constexpr int DC_YP = 32 + 8;    // bf16 per row of group sums and m V^T
-__host__ __device__ constexpr int decode_lds_bytes() { return (2 * D * DC_VP + D * DC_YP) * 2; }
+constexpr int DC_NW = HB_NW;  // wavefronts per workgroup
+__host__ __device__ constexpr int decode_lds_bytes() { return hb_lds_bytes(); }
 
 __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dsm[];
-  uint16_t(*vl)[D][DC_VP] = reinterpret_cast<uint16_t(*)[D][DC_VP]>(dsm);            // [part][row][32 slot + place]
-  uint16_t(*yl)[DC_YP] = reinterpret_cast<uint16_t(*)[DC_YP]>(dsm + 2 * D * DC_VP * 2);  // [row][8 slot + element]
+  uint16_t(*vl)[D][HB_VP] = reinterpret_cast<uint16_t(*)[D][HB_VP]>(dsm);            // [part][row][32 slot + place]
+  uint16_t(*yl)[HB_YP] = reinterpret_cast<uint16_t(*)[HB_YP]>(dsm + 2 * D * HB_VP * 2);  // [row][8 slot + element]
   __shared__ float vmax[DC_NW][NG];
   __shared__ __attribute__((aligned(16))) float scl[DC_NW][TILE];  // a slot's scales of each wavefront's tile
   const int s = blockIdx.y;
@@ -398,74 +396,9 @@ __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
       if (sl < K.n) load_slot(sl, tile);
   }
 
-  // ---- basis to LDS: thread = (channel tid / 4, group tid % 4) ----
   float exps[NG];  // per slot: 2^-e of its scale 2^e
-  {
-    const int ch = tid >> 2, g = tid & 3;
-    const int row = 32 * (ch & 3) + (ch >> 2);  // column c of block b is channel 4c + b
-    const float* vr = a.basis + (int64_t)s * D * D + (int64_t)ch * D + G * g;
-    const float* mr = a.mean + (int64_t)s * D + G * g;
-    float v[32], m[32];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(&v[4 * i]) = *reinterpret_cast<const f32x4*>(vr + 4 * i);
-#pragma unroll
-    for (int i = 0; i < 32; ++i) m[i] = mr[i];
-    float sum = 0.0f, bias = 0.0f, big = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      sum += v[i];
-      bias = __builtin_fmaf(m[i], v[i], bias);
-      big = __builtin_fmaxf(big, __builtin_fabsf(v[i]));
-    }
-    bias += __shfl_xor(bias, 1);
-    bias += __shfl_xor(bias, 2);
-#pragma unroll
-    for (int o = 4; o < 64; o <<= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
-    if (lane < NG) vmax[wave][lane] = big;
-    int slot = -1;  // kept slot of group g
-#pragma unroll
-    for (int sl = 0; sl < NG; ++sl) slot = (sl < K.n && K.grp[sl] == g) ? sl : slot;
-    __syncthreads();
-    int myexp = 0;
-#pragma unroll
-    for (int sl = 0; sl < NG; ++sl) {
-      float mx = 0.0f;
-#pragma unroll
-      for (int w = 0; w < DC_NW; ++w) mx = __builtin_fmaxf(mx, vmax[w][K.grp[sl]]);
-      const int e = __builtin_amdgcn_readfirstlane(9 - scale_exponent(mx));
-      exps[sl] = __builtin_ldexpf(1.0f, -e);
-      myexp = sl == slot ? e : myexp;
-    }
-    const float sc = __builtin_ldexpf(1.0f, myexp);
-    if (slot >= 0) {
-      // coefficients c and c + 16 are neighbours in K: place 2 (c & 15) + (c >> 4)
-      uint32_t hi[16], lo[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) split2_f16(v[i], v[16 + i], sc, hi[i], lo[i]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        *reinterpret_cast<u32x4*>(&vl[0][row][G * slot + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
-        *reinterpret_cast<u32x4*>(&vl[1][row][G * slot + 8 * q]) = u32x4{lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]};
-      }
-    }
-    // row of the zero-point product: slot k has elements 8k .. 8k + 5 = group-sum parts
-    // 0 0 1 0 1 2 (against z parts 0 1 0 2 1 0); elements 6, 7, 14 hold the parts of m V^T
-    // (against ones); threads of dropped groups fill the slots past the kept ones with zeros
-    uint32_t p0, p1, p2, b0, b1, b2;
-    split3(slot >= 0 ? sum : 0.0f, p0, p1, p2);
-    split3(bias, b0, b1, b2);
-    int rank = 0;  // dropped group: its place among the slots past the kept ones
-#pragma unroll
-    for (int gg = 0; gg < NG; ++gg) {
-      bool kept = false;
-#pragma unroll
-      for (int sl = 0; sl < NG; ++sl) kept = kept || (sl < K.n && K.grp[sl] == gg);
-      rank += (!kept && gg < g) ? 1 : 0;
-    }
-    const int ys = slot >= 0 ? slot : K.n + rank;
-    const uint32_t tail = ys == 0 ? pack2(b0, b1) : ys == 1 ? pack2(b2, 0u) : 0u;
-    *reinterpret_cast<u32x4*>(&yl[row][8 * ys]) = u32x4{pack2(p0, p0), pack2(p1, p0), pack2(p1, p2), tail};
-  }
+  stage_head_basis(a.basis + (int64_t)s * D * D, a.mean + (int64_t)s * D, K, tid, vl, yl, vmax, exps,
+                   [](int ch) { return 32 * (ch & 3) + (ch >> 2); });  // column c of block b is channel 4c + b
   __syncthreads();
 
   uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
@@ -475,19 +408,9 @@ __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
     f32x16 out[2][4];  // [32-token block][32-channel block]
     // zero-point and mean terms: lane = token packs its slots' elements, the half swap makes
     // the operands of both blocks (slots 0 and 1 in K step 0, 2 and 3 in K step 1)
-    uint32_t ze[NG][4];
+    u32x4 ze[NG];
 #pragma unroll
-    for (int sl = 0; sl < NG; ++sl) {
-      uint32_t z0 = 0u, z1 = 0u, z2 = 0u;
-      if (sl < K.n) {
-        const float mid = (float)(1 << (K.bits[sl] - 1));
-        split3(__builtin_fmaf(h2f(meta[sl]), mid, h2f(meta[sl] >> 16)), z0, z1, z2);
-      }
-      ze[sl][0] = pack2(z0, z1);
-      ze[sl][1] = pack2(z0, z2);
-      ze[sl][2] = pack2(z1, z0);
-      ze[sl][3] = sl == 0 ? 0x3F803F80u : sl == 1 ? 0x00003F80u : 0u;
-    }
+    for (int sl = 0; sl < NG; ++sl) ze[sl] = zero_elements(meta[sl], sl < K.n ? K.bits[sl] : 0, zero_tail(sl));
     {
       bf16x8 zop[2][2];  // [K step][block]
 #pragma unroll
