@@ -410,11 +410,8 @@ spectra_status spectra_layer_decode_attention(const spectra_codec* ck, const spe
 
 size_t spectra_attention_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens) {
   if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n_tokens <= 0) return 0;
-  int32_t tpc;
   // one workspace serves both attention entry points (latent, and with rotary embeddings)
-  const int32_t nch = std::max(attention_chunks(batch, n_kv_heads, n_tokens, &tpc),
-                               rope_attention_chunks(batch, n_kv_heads, n_tokens, &tpc, 2));
-  return attention_partial_floats(batch, n_q_heads, nch) * sizeof(float);
+  return attention_partial_floats(batch, n_q_heads, attention_max_chunks(batch, n_kv_heads, n_tokens)) * sizeof(float);
 }
 
 // Checks shared by decode_attention and decode_step; fills everything of AttnArgs
@@ -470,7 +467,6 @@ static spectra_status prepare_attention(const char* name, const spectra_codec* c
   a.Wv = cv->record_words;
   const float sc = softmax_scale > 0.0f ? softmax_scale : 1.0f / std::sqrt((float)kD);
   a.scale_log2 = sc * 1.4426950408889634f;
-  a.n_chunks = attention_chunks(batch, n_kv_heads, n_tokens, &a.tiles_per_chunk);
   a.partial = reinterpret_cast<float*>(workspace);
   a.out = out;
   *args = a;

@@ -241,6 +241,11 @@ __device__ __forceinline__ float prepare_query(const AttnArgs& a, int s, int b, 
   return __builtin_ldexpf(1.0f, -E);
 }
 
+// Bytes of LDS that the scan kernel declares itself (operands, Qbar, merge states).
+__host__ __device__ constexpr int attn_static_lds(int nq) {
+  return nq * QA_QUAD * 4 + 16 * 4 * 4 + WAVES * 4 * nq * (2 + NG) * 4 + WAVES * 4 + 64;
+}
+
 // Bytes of LDS holding the softmax-weight rows of all wavefronts: per wave and kept
 // slot, 2*NH rows (hi parts of the NH heads, then lo parts) of 64 bf16 tokens.
 __host__ __device__ constexpr int attn_wt_bytes(int nq) { return WAVES * NG * (8 * nq) * WROW * 2; }
@@ -461,9 +466,10 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a) {
       }
     }
   };
+  int64_t tt = tile_begin + wave;
+
   // In a decode step the workgroup of the last chunk (the last tile) first appends
   // the new token of its stream (and makes the records visible to its own loads).
-  int64_t tt = tile_begin + wave;
   if (a.app_k != nullptr && last_chunk) {
     if (a.app_f32)
       append_token<true>(a, s, tid, reinterpret_cast<uint8_t*>(smem));
@@ -779,25 +785,55 @@ using namespace spectra_dev;
 size_t attention_partial_floats(int32_t batch, int32_t n_q_heads, int32_t n_chunks) {
   return (size_t)batch * n_q_heads * n_chunks * PART;
 }
-// Split of each (sequence, kv head) token range into chunks of whole tiles: about
-// 768 workgroups of four wavefronts, >= 4 tiles per wavefront, over all tiles but
-// the last; the last tile is a chunk of its own (in a decode step its workgroup
-// also appends the new token).
-int32_t attention_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens, int32_t* tiles_per_chunk) {
+// Chunks per (sequence, kv head) that the workspace has room for.
+int32_t attention_max_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens) {
   const int64_t n_tiles = (n_tokens + 63) / 64;
   const int64_t body = n_tiles > 0 ? n_tiles - 1 : 0;
   const int64_t groups = (int64_t)batch * n_kv_heads;
   const int64_t want = (768 + groups - 1) / groups;
   int64_t tpc = (body + want - 1) / want;
   if (tpc < 16) tpc = 16;
-  if (tpc > body) tpc = body > 0 ? body : 1;
   const int64_t nch = (body + tpc - 1) / tpc + 1;
-  *tiles_per_chunk = (int32_t)tpc;
-  return (int32_t)nch;
+  int32_t rope_tpc;
+  const int32_t rope = rope_attention_chunks(batch, n_kv_heads, n_tokens, &rope_tpc, 2);
+  return nch > rope ? (int32_t)nch : rope;
+}
+
+// Split of each (sequence, kv head) token range into chunks of whole tiles for a card that
+// holds `slots` of the scan's workgroups at once: as many chunks as fill those slots, of at
+// least MIN_TILES tiles (two per wavefront), small ones of whole rounds of the four
+// wavefronts. A few workgroups beyond the slots start when the others end and nearly double
+// the scan's time (32k tokens at 4x, 512 slots: 520 workgroups 33.5 us, 352 workgroups 26.5),
+// so the count is rounded down, over the fewest rounds of workgroups that come out 85% full.
+// The last tile is a chunk of its own (in a decode step its workgroup also appends the new
+// token), inside the slots when the slot that it takes costs the other chunks less than one
+// tile per wavefront, otherwise queued behind them.
+// Calls, against chunks of at least 16 tiles for 768 workgroups: 32k tokens at 4x 35.2 ->
+// 31.5 us, seven heads over 65k tokens 34.2 -> 30.9, 1000 tokens 23.8 -> 22.8; equal at 131k
+// tokens (38.5 and 38.2). Chunks of four tiles are no faster at 1000 tokens and 2.5 us slower
+// at 16k (every workgroup prepares the queries).
+constexpr int MIN_TILES = 8;
+static void split_chunks(AttnArgs& a, int slots) {
+  const int64_t body = (a.n_tokens + 63) / 64 - 1;
+  const int64_t groups = (int64_t)a.batch * a.n_kv_heads;
+  int64_t n = 0;
+  for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+    n = rounds * slots / groups;
+    if (n * groups * 100 >= 85 * rounds * slots) break;
+  }
+  if (n > 1 && body < WAVES * n * n) --n;
+  const int64_t cap = attention_max_chunks(a.batch, a.n_kv_heads, a.n_tokens) - 1, most = (body + MIN_TILES - 1) / MIN_TILES;
+  if (n > cap) n = cap;
+  if (n > most) n = most;
+  if (n < 1) n = body > 0 ? 1 : 0;
+  int64_t tpc = n > 0 ? (body + n - 1) / n : 1;
+  if (tpc < 16) tpc = (tpc + WAVES - 1) / WAVES * WAVES;
+  a.tiles_per_chunk = (int32_t)tpc;
+  a.n_chunks = (int32_t)((body + tpc - 1) / tpc) + 1;
 }
 
 template <int NQ, int PK, int PV, bool EXACT>
-static void launch_nq_pw(const AttnArgs& a, hipStream_t st) {
+static int32_t launch_nq_pw(const AttnArgs& a, hipStream_t st) {
   const int wpw = PK > 0 ? PK + PV : a.Wk + a.Wv;
   size_t tiles = (size_t)WAVES * wpw * TROW * 4 + (size_t)attn_wt_bytes(NQ);
   size_t merge = (size_t)WAVES * (NQ <= 2 ? 8 * NQ : 4 * NQ) * AROW * 4;  // per-wave value sums
@@ -807,8 +843,14 @@ static void launch_nq_pw(const AttnArgs& a, hipStream_t st) {
   // more (sequence, kv head) groups than XCDs: chunks of a group kept on one XCD
   AttnArgs g = a;
   g.group_major = a.n_kv_heads * a.batch > 8 ? 1 : 0;
-  const dim3 grid = g.group_major ? dim3(a.n_chunks * a.n_kv_heads * a.batch, 1, 1) : dim3(a.n_chunks, a.n_kv_heads, a.batch);
+  // workgroups a CU holds: three wavefronts per SIMD by the registers of the shapes with one
+  // head quad and at most 24 prefetched words, two for the others; and its 160 KB of LDS
+  constexpr int REGS = NQ == 1 && PK + PV <= 24 ? 3 : 2;
+  const int fit = (int)(160 * 1024 / (lds + attn_static_lds(NQ)));
+  split_chunks(g, 256 * (fit < 1 ? 1 : fit < REGS ? fit : REGS));
+  const dim3 grid = g.group_major ? dim3(g.n_chunks * a.n_kv_heads * a.batch, 1, 1) : dim3(g.n_chunks, a.n_kv_heads, a.batch);
   hipLaunchKernelGGL((attn_kernel<NQ, PK, PV, EXACT>), grid, dim3(256), lds, st, g);
+  return g.n_chunks;
 }
 
 // Prefetch shapes. Up to eight query heads per KV head, records of unequal width
@@ -816,7 +858,7 @@ static void launch_nq_pw(const AttnArgs& a, hipStream_t st) {
 // or three quarters to the keys), otherwise (8, 16) or (16, 8); at most 24
 // prefetch registers keep three wavefronts per SIMD.
 template <int NQ>
-static void launch_nq(const AttnArgs& a, hipStream_t st) {
+static int32_t launch_nq(const AttnArgs& a, hipStream_t st) {
   const int wk = a.Wk, wv = a.Wv;
   if constexpr (NQ <= 2) {
     if (wk == 4 && wv == 12) return launch_nq_pw<NQ, 4, 12, true>(a, st);
@@ -825,15 +867,14 @@ static void launch_nq(const AttnArgs& a, hipStream_t st) {
     if (wv <= 8 && wk > 8 && wk <= 16) return launch_nq_pw<NQ, 16, 8, false>(a, st);
   }
   if (wk == 8 && wv == 8)
-    launch_nq_pw<NQ, 8, 8, true>(a, st);
-  else if (wk <= 8 && wv <= 8)
-    launch_nq_pw<NQ, 8, 8, false>(a, st);
-  else if (wk == 16 && wv == 16)
-    launch_nq_pw<NQ, 16, 16, true>(a, st);
-  else if (wk <= 16 && wv <= 16)
-    launch_nq_pw<NQ, 16, 16, false>(a, st);
-  else
-    launch_nq_pw<NQ, 0, 0, false>(a, st);
+    return launch_nq_pw<NQ, 8, 8, true>(a, st);
+  if (wk <= 8 && wv <= 8)
+    return launch_nq_pw<NQ, 8, 8, false>(a, st);
+  if (wk == 16 && wv == 16)
+    return launch_nq_pw<NQ, 16, 16, true>(a, st);
+  if (wk <= 16 && wv <= 16)
+    return launch_nq_pw<NQ, 16, 16, false>(a, st);
+  return launch_nq_pw<NQ, 0, 0, false>(a, st);
 }
 
 hipError_t launch_combine(const AttnArgs& a, hipStream_t st) {
@@ -841,20 +882,18 @@ hipError_t launch_combine(const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-static hipError_t launch_scan_combine(const AttnArgs& a, hipStream_t st) {
-  switch ((a.n_qh + 3) / 4) {
-    case 1: launch_nq<1>(a, st); break;
-    case 2: launch_nq<2>(a, st); break;
-    case 3: launch_nq<3>(a, st); break;
-    default: launch_nq<4>(a, st); break;
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_combine(a, st);
-}
-
 // Decode-step attention; with a.app_k set, the decode step (append first): the
 // scan kernel, then the chunk combine.
-hipError_t launch_attention(const AttnArgs& a, hipStream_t st) { return launch_scan_combine(a, st); }
+hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
+  AttnArgs g = a;
+  switch ((a.n_qh + 3) / 4) {
+    case 1: g.n_chunks = launch_nq<1>(a, st); break;
+    case 2: g.n_chunks = launch_nq<2>(a, st); break;
+    case 3: g.n_chunks = launch_nq<3>(a, st); break;
+    default: g.n_chunks = launch_nq<4>(a, st); break;
+  }
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_combine(g, st) : e;
+}
 
 }  // namespace spectra
