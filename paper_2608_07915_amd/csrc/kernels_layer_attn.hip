@@ -332,7 +332,8 @@ __global__ __launch_bounds__(512, 4) void layer_values_kernel(LayerAttnArgs a) {
     if (tid < Hq)
       for (int c = 2 * chunk; c < 2 * chunk + 2 && c < a.n_chunks; ++c)
         m = __builtin_fmaxf(m, a.cmax[((int64_t)b * a.n_chunks + c) * Hq + tid]);
-    mh[tid] = m;
+    // where every score of the two chunks is -inf the weights are exp2(-inf - 0) = 0, not NaN
+    mh[tid] = m == -__builtin_inff() ? 0.0f : m;
   }
   if (tid < LA_ROW) rec[WP * LA_ROW + tid] = 0u;
   __syncthreads();
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(512, 4) void layer_values_kernel(LayerAttnArgs a) {
 #pragma unroll
   for (int i = 0; i < PS; ++i) {
     lacc[i] = 0.0f;
-    mref[i] = 16 * hbk + wave + 8 * i < Hq ? mh[16 * hbk + wave + 8 * i] : 0.0f;
+    mref[i] = mh[16 * hbk + wave + 8 * i];
   }
   // the rows of this workgroup's slots: metadata row per slot, payload rows [row_lo, row_hi)
   const int row_lo = half ? __builtin_amdgcn_readfirstlane(tab.pay[8]) : nk;
@@ -552,7 +553,7 @@ __global__ __launch_bounds__(256) void layer_combine_kernel(LayerAttnArgs a) {
     const float L = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
     const float inv_l = L > 0.0f ? 1.0f / L : 0.0f;
     float c = 0.0f;
-    if (kept)
+    if (kept && M != -__builtin_inff())  // no score above -inf: no weight, the output is the mean's
       c = (((ps[0][tid] + ps[1][tid]) + (ps[2][tid] + ps[3][tid])) + ((red[2][0] + red[2][1]) + (red[2][2] + red[2][3]))) *
           inv_l;
     if (a.lscale_v) c /= a.lscale_v[(int64_t)b * d + j];

@@ -47,3 +47,26 @@ def test_layer_attention_edges(d, kw, vw, T, batch, hq, split):
         want = O.attention_mode_a(q[b].astype(np.float64), split_heads(kh[b]), split_heads(vh[b]))
         for h in range(hq):
             assert rel_l2(out[b, h], want[h]) <= ATTN_SAME_TOL
+
+
+@pytest.mark.parametrize("T,masked", [(700, 521), (700, 700), (300, 40), (2100, 2049)])
+def test_layer_attention_minus_infinity_scores(T, masked):
+    """Keys whose zero point is -inf score -inf for queries with positive sums: they weigh
+    nothing, also where every score of a token range is -inf, and where no token is left the
+    output is the mean's row."""
+    rng = np.random.default_rng([T, masked])
+    d, n_kv = 512, 4
+    ck, pk, cap, kh = make_layer_cache(rng, d, [4] + [0] * 7, T, 0, 1)
+    cv, pv, _, vh = make_layer_cache(rng, d, [3, 2] + [0] * 6, T, 0, 1)
+    at = torch.from_numpy(O.physical_index(0, np.arange(masked), 0, cap, ck.record_words)).cuda()
+    pk[at] = (pk[at] & 0xFFFF) | -(0x400 << 16)  # fp16 -inf in the upper half
+    q = np.repeat(ck.basis[0, :, :64].sum(1).cpu().numpy().reshape(n_kv, 128), 2, 0) * rng.uniform(0.05, 0.2, (8, 1))
+    q = q.astype(np.float32)
+    out = S.spectra_layer_decode_attention(ck, cv, pk, pv, cap, T, torch.from_numpy(q[None]).cuda(), n_kv).cpu().numpy()[0]
+    if masked == T:
+        want = np.repeat((cv.mean[0].double() @ cv.basis[0].double().T).cpu().numpy().reshape(n_kv, 128), 2, 0)
+    else:
+        split_heads = lambda x: x[masked:].reshape(T - masked, n_kv, 128).transpose(1, 0, 2)  # noqa: E731
+        want = O.attention_mode_a(q.astype(np.float64), split_heads(kh[0]), split_heads(vh[0]))
+    for h in range(8):
+        assert rel_l2(out[h], want[h]) <= ATTN_SAME_TOL
