@@ -133,6 +133,10 @@ __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis
   uint32_t p0, p1, p2, b0, b1, b2;
   split3(slot >= 0 ? sum : 0.0f, p0, p1, p2);
   split3(bias, b0, b1, b2);
+  if (!(__builtin_fabsf(bias) < __builtin_inff())) {  // not finite: the first part alone (inf - inf is NaN)
+    b0 = __float_as_uint(bias) >> 16;
+    b1 = b2 = 0u;
+  }
   int rank = 0;  // dropped group: its place among the slots past the kept ones
 #pragma unroll
   for (int gg = 0; gg < NG; ++gg) {

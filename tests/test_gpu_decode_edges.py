@@ -38,3 +38,15 @@ def test_decode_edges(widths, T, t0, n, scale):
     got = S.spectra_decode(codec, packed, t_cap, t0, T).cpu().numpy()
     for s in range(n):
         assert rel_l2(got[s], want[s]) <= 1e-6
+
+
+def test_decode_infinite_mean():
+    """An infinite mean coefficient makes every row of its stream infinite, with the sign of the
+    channel's basis entry; other streams stay finite."""
+    rng = np.random.default_rng(5)
+    codec, packed, t_cap, want = make_layer_cache(rng, 128, [3, 2, 0, 1], 70, 0, 2, g=32)
+    codec.mean[0, 40] = float("inf")
+    got = S.spectra_decode(codec, packed, t_cap, 0, 70).cpu().numpy()
+    sign = np.sign(codec.basis[0, :, 40].cpu().numpy())
+    assert np.array_equal(got[0], np.broadcast_to(sign * np.inf, (70, 128)))
+    assert rel_l2(got[1], want[1]) <= 1e-6
