@@ -228,7 +228,8 @@ spectra_status spectra_layer_decode_attention(const spectra_codec* ck, const spe
  * kept value coefficients, then one inverse rotation (a + m_V) V_V^T.
  * softmax_scale <= 0 selects 1/sqrt(d). n_q_heads / n_kv_heads <= 16;
  * t_capacity * record_words < 2^31 for both codecs.
- * Workspace: device, spectra_attention_workspace_bytes bytes. Asynchronous.
+ * Workspace: device, spectra_attention_workspace_bytes bytes (never fewer for more
+ * tokens: one taken for the longest cache serves every shorter one). Asynchronous.
  * ------------------------------------------------------------------------- */
 size_t spectra_attention_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads,
                                          int64_t n_tokens);
@@ -285,8 +286,9 @@ spectra_status spectra_decode_step(const spectra_codec* ck, const spectra_codec*
  * SPECTRA_STATIC_SCRATCH_BYTES bytes that the library holds on every GPU it runs
  * on until the process ends, instead of a workspace. Calls no hipMalloc/hipFree
  * (the array's address is looked up once per device, on its first call there).
- * Returns SPECTRA_EWORKSPACE when spectra_attention_workspace_bytes(batch,
- * n_q_heads, n_kv_heads, t + 1) exceeds the array. Every call on one GPU shares
+ * Returns SPECTRA_EWORKSPACE when the step's own partials, at most
+ * spectra_attention_workspace_bytes(batch, n_q_heads, n_kv_heads, t + 1) bytes,
+ * exceed the array. Every call on one GPU shares
  * that GPU's array: calls that overlap on one GPU (other streams, other threads)
  * race and must be serialised by the caller. Other arguments and errors as
  * spectra_decode_step. Asynchronous.

@@ -411,7 +411,7 @@ spectra_status spectra_layer_decode_attention(const spectra_codec* ck, const spe
 size_t spectra_attention_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens) {
   if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n_tokens <= 0) return 0;
   // one workspace serves both attention entry points (latent, and with rotary embeddings)
-  return attention_partial_floats(batch, n_q_heads, attention_max_chunks(batch, n_kv_heads, n_tokens)) * sizeof(float);
+  return attention_partial_floats(batch, n_q_heads, attention_workspace_chunks(batch, n_kv_heads, n_tokens)) * sizeof(float);
 }
 
 // Checks shared by decode_attention and decode_step; fills everything of AttnArgs
@@ -443,7 +443,7 @@ static spectra_status prepare_attention(const char* name, const spectra_codec* c
     return fail(SPECTRA_EINVAL, "%s: packed_k / packed_v must be non-null and 4-byte aligned", name);
   if (!(softmax_scale == softmax_scale) || std::isinf(softmax_scale))
     return fail(SPECTRA_EINVAL, "%s: softmax_scale not finite", name);
-  const size_t need = spectra_attention_workspace_bytes(batch, n_q_heads, n_kv_heads, n_tokens);
+  const size_t need = attention_call_bytes(batch, n_q_heads, n_kv_heads, n_tokens);
   if (!workspace || !aligned(workspace, 256)) return fail(SPECTRA_EINVAL, "%s: workspace must be 256-byte aligned", name);
   if (ws_bytes < need) return fail(SPECTRA_EWORKSPACE, "%s: workspace %zu < %zu bytes", name, ws_bytes, need);
   AttnArgs a{};

@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "host_common.hpp"
+#include "kernels.hpp"
 
 namespace {
 
@@ -45,7 +46,7 @@ extern "C" spectra_status spectra_decode_step_static(const spectra_codec* ck, co
                                                      float softmax_scale, float* out, void* stream) {
   if (t < 0 || t >= t_capacity)
     return spectra::fail(SPECTRA_EINVAL, "decode_step_static: slot t=%lld outside [0, t_capacity)", (long long)t);
-  const size_t need = spectra_attention_workspace_bytes(batch, n_q_heads, n_kv_heads, t + 1);
+  const size_t need = spectra::attention_call_bytes(batch, n_q_heads, n_kv_heads, t + 1);
   if (need == 0) return spectra::fail(SPECTRA_EINVAL, "decode_step_static: batch and head counts must be positive");
   if (need > (size_t)SPECTRA_STATIC_SCRATCH_BYTES)
     return spectra::fail(SPECTRA_EWORKSPACE, "decode_step_static: %zu bytes of partials exceed the static %zu bytes",

@@ -119,6 +119,10 @@ int32_t rope_attention_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_token
 // Workspace layout of decode_attention (bytes), shared by the host API and launcher.
 size_t attention_partial_floats(int32_t batch, int32_t n_q_heads, int32_t n_chunks);
 int32_t attention_max_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens);
+int32_t attention_workspace_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens);
+// Bytes of partials that a call over n_tokens needs (0 for counts that are not positive); at
+// most what spectra_attention_workspace_bytes gives for n_tokens or more.
+size_t attention_call_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens);
 // moments[s] = [W_s^T G W_s, hbar W_s] for W [n_streams][d_model][d] fp32 (d a multiple of 64)
 // and per-layer G [layers][d_model][d_model], hbar [layers][d_model] fp64 (layer = s /
 // streams_per_layer); scratch: n_streams * d_model * d doubles.

@@ -785,7 +785,10 @@ using namespace spectra_dev;
 size_t attention_partial_floats(int32_t batch, int32_t n_q_heads, int32_t n_chunks) {
   return (size_t)batch * n_q_heads * n_chunks * PART;
 }
-// Chunks per (sequence, kv head) that the workspace has room for.
+// Chunks per (sequence, kv head) that one call has room for in its workspace: the larger of
+// chunks of at least 16 tiles for 768 workgroups over all tiles but the last, plus that tile's,
+// and the rotary kernels' split. Not monotone in n_tokens: a longer cache can have longer and
+// fewer chunks.
 int32_t attention_max_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens) {
   const int64_t n_tiles = (n_tokens + 63) / 64;
   const int64_t body = n_tiles > 0 ? n_tiles - 1 : 0;
@@ -797,6 +800,22 @@ int32_t attention_max_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens
   int32_t rope_tpc;
   const int32_t rope = rope_attention_chunks(batch, n_kv_heads, n_tokens, &rope_tpc, 2);
   return nch > rope ? (int32_t)nch : rope;
+}
+
+size_t attention_call_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens) {
+  if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n_tokens <= 0) return 0;
+  return attention_partial_floats(batch, n_q_heads, attention_max_chunks(batch, n_kv_heads, n_tokens)) * sizeof(float);
+}
+
+// The most of those over all token counts up to n_tokens, so that a workspace taken for the
+// longest cache serves every shorter one: with chunks of their smallest length, as long as
+// there are no more of them than wanted.
+int32_t attention_workspace_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens) {
+  const int64_t n_tiles = (n_tokens + 63) / 64, groups = (int64_t)batch * n_kv_heads;
+  const int64_t want = (768 + groups - 1) / groups, rope_want = (512 + groups - 1) / groups;
+  const int64_t body = (n_tiles - 1 + 15) / 16, rope = (n_tiles + 3) / 4;
+  const int64_t scan = (body < want ? body : want) + 1, rot = rope < rope_want ? rope : rope_want;
+  return (int32_t)(scan > rot ? scan : rot);
 }
 
 // Split of each (sequence, kv head) token range into chunks of whole tiles for a card that
