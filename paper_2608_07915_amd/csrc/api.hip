@@ -9,6 +9,7 @@
 
 #include "host_common.hpp"
 #include "kernels.hpp"
+#include "splits.hpp"
 #include "layer.hpp"
 
 using namespace spectra;
@@ -411,7 +412,7 @@ spectra_status spectra_layer_decode_attention(const spectra_codec* ck, const spe
 size_t spectra_attention_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens) {
   if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n_tokens <= 0) return 0;
   // one workspace serves both attention entry points (latent, and with rotary embeddings)
-  return attention_partial_floats(batch, n_q_heads, attention_workspace_chunks(batch, n_kv_heads, n_tokens)) * sizeof(float);
+  return attention_partial_floats(batch, n_q_heads, attention_workspace_chunks((int64_t)batch * n_kv_heads, (n_tokens + 63) / 64)) * sizeof(float);
 }
 
 // Checks shared by decode_attention and decode_step; fills everything of AttnArgs

@@ -112,14 +112,10 @@ hipError_t launch_attention(const spectra_dev::AttnArgs& a, hipStream_t st);
 // Merge of the chunk partials in a.partial into a.out (+ m_V, inverse value rotation).
 hipError_t launch_combine(const spectra_dev::AttnArgs& a, hipStream_t st);
 // Attention with rotary position embeddings (Mode A keys, latent values), then the
-// combine; chunk split from rope_attention_chunks.
+// combine; kernel and chunk split from rope_split.
 hipError_t launch_attention_rope(const spectra_dev::AttnArgs& a, hipStream_t st);
-int32_t rope_attention_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens, int32_t* tiles_per_chunk,
-                              int32_t per_cu);
 // Workspace layout of decode_attention (bytes), shared by the host API and launcher.
 size_t attention_partial_floats(int32_t batch, int32_t n_q_heads, int32_t n_chunks);
-int32_t attention_max_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens);
-int32_t attention_workspace_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens);
 // Bytes of partials that a call over n_tokens needs (0 for counts that are not positive); at
 // most what spectra_attention_workspace_bytes gives for n_tokens or more.
 size_t attention_call_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens);

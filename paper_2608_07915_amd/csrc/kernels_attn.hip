@@ -31,6 +31,7 @@
 #include "device_common.hpp"
 #include "encode_dev.hpp"
 #include "kernels.hpp"
+#include "splits.hpp"
 #include "kplan.hpp"
 
 namespace spectra_dev {
@@ -785,37 +786,9 @@ using namespace spectra_dev;
 size_t attention_partial_floats(int32_t batch, int32_t n_q_heads, int32_t n_chunks) {
   return (size_t)batch * n_q_heads * n_chunks * PART;
 }
-// Chunks per (sequence, kv head) that one call has room for in its workspace: the larger of
-// chunks of at least 16 tiles for 768 workgroups over all tiles but the last, plus that tile's,
-// and the rotary kernels' split. Not monotone in n_tokens: a longer cache can have longer and
-// fewer chunks.
-int32_t attention_max_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens) {
-  const int64_t n_tiles = (n_tokens + 63) / 64;
-  const int64_t body = n_tiles > 0 ? n_tiles - 1 : 0;
-  const int64_t groups = (int64_t)batch * n_kv_heads;
-  const int64_t want = (768 + groups - 1) / groups;
-  int64_t tpc = (body + want - 1) / want;
-  if (tpc < 16) tpc = 16;
-  const int64_t nch = (body + tpc - 1) / tpc + 1;
-  int32_t rope_tpc;
-  const int32_t rope = rope_attention_chunks(batch, n_kv_heads, n_tokens, &rope_tpc, 2);
-  return nch > rope ? (int32_t)nch : rope;
-}
-
 size_t attention_call_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int64_t n_tokens) {
   if (batch <= 0 || n_q_heads <= 0 || n_kv_heads <= 0 || n_tokens <= 0) return 0;
-  return attention_partial_floats(batch, n_q_heads, attention_max_chunks(batch, n_kv_heads, n_tokens)) * sizeof(float);
-}
-
-// The most of those over all token counts up to n_tokens, so that a workspace taken for the
-// longest cache serves every shorter one: with chunks of their smallest length, as long as
-// there are no more of them than wanted.
-int32_t attention_workspace_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens) {
-  const int64_t n_tiles = (n_tokens + 63) / 64, groups = (int64_t)batch * n_kv_heads;
-  const int64_t want = (768 + groups - 1) / groups, rope_want = (512 + groups - 1) / groups;
-  const int64_t body = (n_tiles - 1 + 15) / 16, rope = (n_tiles + 3) / 4;
-  const int64_t scan = (body < want ? body : want) + 1, rot = rope < rope_want ? rope : rope_want;
-  return (int32_t)(scan > rot ? scan : rot);
+  return attention_partial_floats(batch, n_q_heads, attention_max_chunks((int64_t)batch * n_kv_heads, (n_tokens + 63) / 64)) * sizeof(float);
 }
 
 // Split of each (sequence, kv head) token range into chunks of whole tiles for a card that
@@ -841,7 +814,7 @@ static void split_chunks(AttnArgs& a, int slots) {
     if (n * groups * 100 >= 85 * rounds * slots) break;
   }
   if (n > 1 && body < WAVES * n * n) --n;
-  const int64_t cap = attention_max_chunks(a.batch, a.n_kv_heads, a.n_tokens) - 1, most = (body + MIN_TILES - 1) / MIN_TILES;
+  const int64_t cap = attention_max_chunks(groups, body + 1) - 1, most = (body + MIN_TILES - 1) / MIN_TILES;
   if (n > cap) n = cap;
   if (n > most) n = most;
   if (n < 1) n = body > 0 ? 1 : 0;

@@ -8,7 +8,8 @@
 // Three kernels. rope_attn_wave_kernel (the common shapes: up to four query heads per KV head
 // with records of at most 16 words, up to eight with at most 8; at the end of the file)
 // gives every wavefront its own tiles; rope_attn4_kernel (five to eight heads, 9 to 16
-// words) shares a tile among four wavefronts and keeps the rebuilt keys in registers.
+// words, and some chunk lengths with fewer) shares a tile among four wavefronts and keeps the
+// rebuilt keys in registers.
 // rope_attn_kernel serves the wider records: one workgroup of eight wavefronts per
 // (token chunk, KV head, sequence), 64-token tiles, three workgroup barriers per tile.
 // While tile tt is processed, the record words of tile tt + 1 are staged and its key codes
@@ -31,6 +32,7 @@
 #include "device_common.hpp"
 #include "encode_dev.hpp"
 #include "kernels.hpp"
+#include "splits.hpp"
 
 namespace spectra_dev {
 
@@ -497,9 +499,10 @@ __global__ __launch_bounds__(RTHREADS, 1) void rope_attn_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Four-wavefront form (five to eight query heads per KV head, records of 9 to 16 words,
-// whose buffers do not fit the wavefront form's LDS): two workgroups per CU, two workgroup barriers per tile, the reconstructed
-// keys never leave the registers.
+// Four-wavefront form (five to eight query heads per KV head, records of 9 to 16 words, whose
+// buffers do not fit the wavefront form's LDS, or chunks whose last step would leave that
+// form's wavefronts idle): two workgroups per CU, two workgroup barriers per tile, the
+// reconstructed keys never leave the registers.
 //   1. wavefront w reconstructs dimensions 16w..16w+15 and 64+16w..64+16w+15 of the
 //      tile's 64 tokens on v_mfma_f32_32x32x16_bf16 (rows m and m + 16 of its 32-row
 //      output are the pair (i, i + 64) with i = 16w + m, so a lane holds both
@@ -944,6 +947,7 @@ __global__ __launch_bounds__(R4T, 2) void rope_attn4_kernel(AttnArgs a) {
 // chain per SIMD pair waits.
 // ---------------------------------------------------------------------------
 constexpr int RW_NW = HB_NW;
+static_assert(RW_NW == spectra::ROPE_WAVE_TILES, "a tile per wavefront");
 constexpr int RW_TP = 66;  // (cos, sin) pairs per row of the in-block rotation table (64 frequencies + pad: 16-byte rows)
 __host__ __device__ constexpr int rw_query_bytes(int nh) { return 64 * nh * 8 > 2 * nh * WROW * 2 ? 64 * nh * 8 : 2 * nh * WROW * 2; }
 __host__ __device__ constexpr int rw_off_tab() { return hb_lds_bytes(); }
@@ -1340,35 +1344,19 @@ __global__ __launch_bounds__(64 * RW_NW, 2) void rope_attn_wave_kernel(AttnArgs 
 namespace spectra {
 using namespace spectra_dev;
 
-// About per_cu workgroups per CU in one round, at least four tiles per chunk.
-int32_t rope_attention_chunks(int32_t batch, int32_t n_kv_heads, int64_t n_tokens, int32_t* tiles_per_chunk,
-                              int32_t per_cu) {
-  const int64_t n_tiles = (n_tokens + 63) / 64;
-  const int64_t groups = (int64_t)batch * n_kv_heads;
-  const int64_t want = (256 * (int64_t)per_cu + groups - 1) / groups;
-  int64_t tpc = (n_tiles + want - 1) / want;
-  if (tpc < 4) tpc = 4;
-  *tiles_per_chunk = (int32_t)tpc;
-  return (int32_t)((n_tiles + tpc - 1) / tpc);
-}
-
-// The wavefront kernel where its LDS fits a CU, there the faster one at every size timed
-// (131k tokens, four heads: 119 us against 183; 65k, seven heads: 68 against 77; 1000
-// tokens: 29 against 37): at most four query heads per KV head with records of at most 16
-// words, at most eight with records of at most 8. Eight heads with 9 to 16 words need more
-// than 160 KB there, so they take the four-wavefront kernel (two workgroups per CU), and
-// wider records the eight-wavefront kernel.
 hipError_t launch_attention_rope(const AttnArgs& a, hipStream_t st) {
   int dev = 0, lds = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
   const int nh = a.n_qh <= 4 ? 4 : 8, w = a.Wk > a.Wv ? a.Wk : a.Wv;
-  const bool by_wave = a.n_qh <= 8 && w <= (nh == 4 ? 16 : 8), four = !by_wave && a.n_qh <= 8 && w <= R4W;
+  const RopeSplit rs = rope_split((int64_t)a.batch * a.n_kv_heads, a.n_qh, w, (a.n_tokens + 63) / 64);
+  const bool by_wave = rs.kernel == RopeKernel::WAVE, four = rs.kernel == RopeKernel::FOUR;
   // the tile buffers need more than 64 KB of LDS: refuse a device that has less
   if (lds < (by_wave ? rw_lds_bytes(nh, w <= 8 ? 8 : 16) : four ? r4_lds_bytes(nh) : rope_lds_bytes(nh))) return hipErrorInvalidConfiguration;
   AttnArgs g = a;
-  g.n_chunks = rope_attention_chunks(a.batch, a.n_kv_heads, a.n_tokens, &g.tiles_per_chunk, four ? 2 : 1);
+  g.n_chunks = rs.split.n_chunks;
+  g.tiles_per_chunk = rs.split.tiles_per_chunk;
   const dim3 grid(g.n_chunks, g.n_kv_heads, g.batch);
   if (by_wave) {
     if (nh == 8)

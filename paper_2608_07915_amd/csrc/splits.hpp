@@ -1,0 +1,98 @@
+// How the kernels' grids split tokens over workgroups (plain C++17, shared by the launchers
+// and host-side checks). A workgroup that starts when the others end costs a whole round, so
+// no grid is rounded up past what the card's CUs hold at once.
+#pragma once
+#include <cstdint>
+
+namespace spectra {
+
+constexpr int64_t N_CU = 256;  // compute units of the card
+
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Chunk c of a token range: tiles [c tiles_per_chunk, (c + 1) tiles_per_chunk).
+struct Split {
+  int32_t tiles_per_chunk, n_chunks;
+};
+inline Split split_tiles(int64_t n_tiles, int64_t tiles_per_chunk) {
+  return Split{(int32_t)tiles_per_chunk, (int32_t)ceil_div(n_tiles, tiles_per_chunk)};
+}
+
+// ---------------------------------------------------------------------------
+// Workspace of the per-head attention calls, in chunks per (sequence, KV head)
+// ---------------------------------------------------------------------------
+// What one call has room for: the larger of chunks of at least 16 tiles for 768 workgroups
+// over all tiles but the last, plus that tile's, and chunks of at least four tiles for 512. Not
+// monotone in the tiles: a longer cache can have longer and fewer chunks.
+inline int32_t attention_max_chunks(int64_t groups, int64_t n_tiles) {
+  const int64_t body = n_tiles > 0 ? n_tiles - 1 : 0;
+  int64_t tpc = ceil_div(body, ceil_div(768, groups)), rope_tpc = ceil_div(n_tiles, ceil_div(2 * N_CU, groups));
+  if (tpc < 16) tpc = 16;
+  if (rope_tpc < 4) rope_tpc = 4;
+  const int64_t scan = ceil_div(body, tpc) + 1, rope = ceil_div(n_tiles, rope_tpc);
+  return (int32_t)(scan > rope ? scan : rope);
+}
+
+// The most of those over all caches of up to n_tiles tiles, so that a workspace taken for the
+// longest cache serves every shorter one: chunks of their smallest length, as long as there
+// are no more of them than wanted.
+inline int32_t attention_workspace_chunks(int64_t groups, int64_t n_tiles) {
+  const int64_t want = ceil_div(768, groups), rope_want = ceil_div(2 * N_CU, groups);
+  const int64_t body = ceil_div(n_tiles - 1, 16), rope = ceil_div(n_tiles, 4);
+  const int64_t scan = (body < want ? body : want) + 1, rot = rope < rope_want ? rope : rope_want;
+  return (int32_t)(scan > rot ? scan : rot);
+}
+
+// ---------------------------------------------------------------------------
+// Rotary attention
+// ---------------------------------------------------------------------------
+enum class RopeKernel { WAVE, FOUR, EIGHT };  // a tile per wavefront, per four, per eight wavefronts
+struct RopeSplit {
+  RopeKernel kernel;
+  Split split;
+};
+constexpr int ROPE_WAVE_TILES = 8;  // tiles that a workgroup of the wavefront kernel takes at a time
+
+// Split for a kernel of which a CU holds per_cu workgroups, each taking `at_once` tiles of its
+// chunk at a time: as many chunks of at least four tiles as one round of workgroups holds, or
+// two rounds of one workgroup per CU, whichever has fewer steps (the preparation counts as one
+// and a third). With the count rounded up, 12 groups (28 query heads on 4 KV heads, batch 3)
+// made 264 workgroups for 256 CUs: 32k tokens 155 us, now 90; eight KV heads at batch 5 220 us,
+// now 150 (four wavefronts per tile, before: 105 and 338).
+inline Split rope_chunks(int64_t groups, int64_t n_tiles, int per_cu, int at_once) {
+  Split best{};
+  int64_t best_cost = 0;
+  for (int rounds = 1; rounds * per_cu <= 2; ++rounds) {
+    int64_t n = N_CU * per_cu * rounds / groups;
+    if (n < 1) n = 1;
+    int64_t tpc = ceil_div(n_tiles, n);
+    if (tpc < 4) tpc = 4;
+    const Split s = split_tiles(n_tiles, tpc);
+    const int64_t cost = ceil_div(s.n_chunks * groups, N_CU * per_cu) * (4 + 3 * ceil_div(tpc, at_once));
+    if (rounds == 1 || cost < best_cost) {
+      best_cost = cost;
+      best = s;
+    }
+  }
+  return best;
+}
+
+// Up to four query heads per KV head with records of at most 16 words and up to eight with at
+// most 8 words fit the wavefront kernel's LDS, and it is the faster one (131k tokens, four
+// heads: 119 us against 183; 65k, seven heads: 65 against 76; 1000 tokens: 29 against 37), but
+// for seven heads where its chunks have nine or ten tiles: the second step of eight wavefronts
+// then has one or two at work (57.5 us against 56.5 at 9 tiles and one sequence, 63 against 58
+// at 10 and four). The other shapes of up to 16 words take the four-wavefront kernel (two
+// workgroups per CU), wider records the eight-wavefront kernel.
+inline RopeSplit rope_split(int64_t groups, int n_qh, int words, int64_t n_tiles) {
+  const bool few = n_qh <= 4;
+  if (words <= (few ? 16 : 8)) {
+    const Split s = rope_chunks(groups, n_tiles, 1, ROPE_WAVE_TILES);
+    const int t = s.tiles_per_chunk;
+    if (few || t <= ROPE_WAVE_TILES || t > ROPE_WAVE_TILES + 2) return RopeSplit{RopeKernel::WAVE, s};
+  }
+  if (!few && words <= 16) return RopeSplit{RopeKernel::FOUR, rope_chunks(groups, n_tiles, 2, 1)};
+  return RopeSplit{RopeKernel::EIGHT, rope_chunks(groups, n_tiles, 1, 1)};
+}
+
+}  // namespace spectra

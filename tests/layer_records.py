@@ -40,3 +40,12 @@ def make_layer_cache(rng, d, widths, T, t0, n, scale=1.0, split=False, stale=Tru
             codec.lscale[s].copy_(torch.from_numpy(f))
         rows.append(O.decode(rec, basis, mean, bits, p, f))
     return codec, torch.from_numpy(words.view(np.int32)).cuda(), t_cap, rows
+
+
+def repeat_streams(codec, packed, r):
+    """The codec and records with all streams r times over."""
+    import torch
+    out = S.Codec(codec.params, codec.n_streams * r, latent_scale=codec.lscale is not None)
+    for name in ("basis", "mean", "bits") + (("lscale",) if codec.lscale is not None else ()):
+        getattr(out, name).copy_(torch.cat([getattr(codec, name)] * r))
+    return out, packed.repeat(r)

@@ -1,0 +1,55 @@
+// Host check of the grid splits (splits.hpp) over token counts and (sequence, KV head) groups:
+// every tile in exactly one chunk and no chunk empty, no more chunks than a call's workspace
+// holds, and no workgroups left over for a round of their own.
+#include <cstdio>
+#include <initializer_list>
+
+#include "splits.hpp"
+
+using namespace spectra;
+
+static int bad = 0;
+#define CHECK(cond, ...)                \
+  do {                                  \
+    if (!(cond)) {                      \
+      if (++bad < 20) {                 \
+        std::printf("%s: ", #cond);     \
+        std::printf(__VA_ARGS__);       \
+        std::printf("\n");              \
+      }                                 \
+    }                                   \
+  } while (0)
+
+static const int64_t GROUPS[] = {1, 2, 3, 4, 5, 8, 12, 16, 20, 24, 32, 40, 48, 64, 96, 100, 128, 160, 200, 256, 257, 300, 500, 512, 600, 900, 2000};
+
+static void covers(const char* what, int64_t g, int64_t tiles, Split s) {
+  CHECK(s.tiles_per_chunk > 0 && s.n_chunks > 0 && (int64_t)s.n_chunks * s.tiles_per_chunk >= tiles &&
+            (int64_t)(s.n_chunks - 1) * s.tiles_per_chunk < tiles,
+        "%s: %lld groups, %lld tiles: %d chunks of %d", what, (long long)g, (long long)tiles, s.n_chunks, s.tiles_per_chunk);
+}
+
+int main() {
+  for (int64_t g : GROUPS) {
+    int32_t most = 0;
+    for (int64_t tiles = 1; tiles < 9000; tiles += tiles < 800 ? 1 : 7) {
+      const int32_t cap = attention_max_chunks(g, tiles), ws = attention_workspace_chunks(g, tiles);
+      CHECK(cap <= ws && ws >= most, "%lld groups, %lld tiles: %d, %d, %d", (long long)g, (long long)tiles, cap, ws, most);
+      most = ws;
+      for (int n_qh = 1; n_qh <= 8; n_qh += 3)
+        for (int words : {4, 8, 9, 16, 17, 32}) {
+          const RopeSplit r = rope_split(g, n_qh, words, tiles);
+          const Split s = r.split;
+          covers("rotary", g, tiles, s);
+          CHECK(s.n_chunks <= cap, "rotary: %lld groups, %lld tiles: %d chunks, room for %d", (long long)g, (long long)tiles, s.n_chunks, cap);
+          const int64_t slots = r.kernel == RopeKernel::FOUR ? 512 : 256, wgs = g * s.n_chunks;
+          CHECK(wgs <= slots || g > slots || wgs > slots + slots / 2, "rotary: %lld groups, %lld tiles: %lld workgroups for %lld slots", (long long)g,
+                (long long)tiles, (long long)wgs, (long long)slots);
+          // what each kernel's buffers hold
+          CHECK(r.kernel != RopeKernel::WAVE || words <= (n_qh <= 4 ? 16 : 8), "wavefront kernel: %d heads, %d words", n_qh, words);
+          CHECK(r.kernel != RopeKernel::FOUR || (n_qh > 4 && words <= 16), "four-wavefront kernel: %d heads, %d words", n_qh, words);
+        }
+    }
+  }
+  if (bad == 0) std::printf("OK\n");
+  return bad ? 1 : 0;
+}

@@ -12,7 +12,7 @@ import pytest
 import oracle as O
 import paper_2608_07915_amd as S
 from gpu_parity import ATTN_SAME_TOL, rel_l2
-from layer_records import make_layer_cache
+from layer_records import make_layer_cache, repeat_streams
 
 pytestmark = pytest.mark.gpu
 
@@ -48,5 +48,40 @@ def test_rope_attention_edges(kw, vw, T, batch, kv, nqh, pos):
         sl = slice(b * kv, (b + 1) * kv)
         want = O.attention_mode_a_rope(q[b].astype(np.float64), np.stack(kh[sl]), np.stack(vh[sl]), w.astype(np.float64),
                                        T - 1 if pos is None else pos)
+        for h in range(kv * nqh):
+            assert rel_l2(out[b, h], want[h]) <= ATTN_SAME_TOL
+
+
+LONG = [
+    # key widths, value widths, tiles, query heads per KV head: 128 (sequence, KV head) groups, so
+    # chunks are half of the tiles
+    ([4, 2, 0, 0], [3, 1, 1, 0], 40, 4),     # a tile per wavefront: two or three tiles each
+    ([5, 3, 2, 2], [2, 3, 4, 3], 40, 3),     # the same with 16-word records
+    ([3, 1, 1, 0], [4, 2, 0, 0], 40, 7),     # eight heads
+    ([3, 1, 1, 0], [4, 2, 0, 0], 19, 7),     # chunks of ten tiles: four wavefronts per tile
+    ([7, 5, 0, 0], [3, 3, 3, 2], 40, 6),     # 16 words, five to eight heads
+    ([8, 6, 4, 2], [8, 8, 3, 1], 12, 4),     # wider records
+]
+
+
+@pytest.mark.parametrize("kw,vw,tiles,nqh", LONG)
+def test_rope_attention_long_chunks(kw, vw, tiles, nqh):
+    """Chunks of several steps of every kernel: the turn from one tile to the next, words
+    loaded ahead, buffers used again, sums rescaled."""
+    rng = np.random.default_rng([tiles, nqh])
+    batch, kv, n, T = 64, 2, 8, 64 * tiles - 23
+    ck, pk, cap, kh = make_layer_cache(rng, 128, kw, T, 0, n, g=32)
+    cv, pv, _, vh = make_layer_cache(rng, 128, vw, T, 0, n, g=32)
+    ck, pk = repeat_streams(ck, pk, batch * kv // n)
+    cv, pv = repeat_streams(cv, pv, batch * kv // n)
+    q = rng.standard_normal((batch, kv * nqh, 128)).astype(np.float32)
+    q *= np.exp(rng.uniform(-2, 1, (batch, kv * nqh, 1))).astype(np.float32)
+    w = (1.0e4 ** (-np.arange(64) / 64)).astype(np.float32)
+    out = S.spectra_decode_attention_rope(ck, cv, pk, pv, cap, T, torch.from_numpy(q).cuda(), kv,
+                                          torch.from_numpy(w).cuda()).cpu().numpy()
+    for b in (0, 1, 33, 63):
+        sl = [(b * kv + h) % n for h in range(kv)]
+        want = O.attention_mode_a_rope(q[b].astype(np.float64), np.stack([kh[s] for s in sl]), np.stack([vh[s] for s in sl]),
+                                       w.astype(np.float64), T - 1)
         for h in range(kv * nqh):
             assert rel_l2(out[b, h], want[h]) <= ATTN_SAME_TOL
