@@ -61,7 +61,7 @@ __device__ __forceinline__ void split2_f16(float x0, float x1, float sc, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// Basis of one KV head in LDS for a workgroup of eight wavefronts: row row_of(ch) of vl
+// Basis of one KV head in LDS for a workgroup of NW (eight or four) wavefronts: row row_of(ch) of vl
 // holds channel ch's entries of the kept groups as two fp16 parts, group slot sl scaled by
 // the power of two that brings its largest entry into [2^8, 2^9) (exps[sl] is the inverse),
 // coefficient c of a group at place 2 (c & 15) + (c >> 4). The same row of yl is the other
@@ -70,34 +70,38 @@ __device__ __forceinline__ void split2_f16(float x0, float x1, float sc, uint32_
 // 0 1 2 of the group's sum, against parts 0 1 0 2 1 0 of zc (zero_elements); elements 6,
 // 7 and 14 hold the parts of m V^T, against ones. The caller synchronises afterwards.
 // ---------------------------------------------------------------------------
-constexpr int HB_NW = 8;         // wavefronts of the workgroup: a thread per (channel, group)
+constexpr int HB_NW = 8;         // wavefronts with a thread per (channel, group)
 constexpr int HB_VP = D + 8;     // fp16 per basis row (272 bytes: 16 rows on distinct banks)
 constexpr int HB_YP = 32 + 8;    // bf16 per row of group sums and m V^T
 __host__ __device__ constexpr int hb_lds_bytes() { return (2 * D * HB_VP + D * HB_YP) * 2; }
 
-template <typename RowFn>
+template <int NW = HB_NW, typename RowFn>
 __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis, const float* __restrict__ mean, const Kept& K,
                                                  int tid, uint16_t (*vl)[D][HB_VP], uint16_t (*yl)[HB_YP],
                                                  float (*vmax)[NG], float (&exps)[NG], RowFn&& row_of) {
+  constexpr int IT = HB_NW / NW;  // channels per thread
   const int wave = tid >> 6, lane = tid & 63;
-  const int ch = tid >> 2, g = tid & 3;
-  const int row = row_of(ch);
-  const float* vr = basis + (int64_t)ch * D + G * g;
-  const float* mr = mean + G * g;
-  float v[32], m[32];
+  const int g = tid & 3;
+  float v[IT][32], sum[IT], bias[IT], big = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(&v[4 * i]) = *reinterpret_cast<const f32x4*>(vr + 4 * i);
+  for (int it = 0; it < IT; ++it) {
+    const float* vr = basis + (int64_t)((tid >> 2) + 16 * NW * it) * D + G * g;
+    const float* mr = mean + G * g;
+    float m[32];
 #pragma unroll
-  for (int i = 0; i < 32; ++i) m[i] = mr[i];
-  float sum = 0.0f, bias = 0.0f, big = 0.0f;
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(&v[it][4 * i]) = *reinterpret_cast<const f32x4*>(vr + 4 * i);
 #pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    sum += v[i];
-    bias = __builtin_fmaf(m[i], v[i], bias);
-    big = __builtin_fmaxf(big, __builtin_fabsf(v[i]));
+    for (int i = 0; i < 32; ++i) m[i] = mr[i];
+    sum[it] = bias[it] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      sum[it] += v[it][i];
+      bias[it] = __builtin_fmaf(m[i], v[it][i], bias[it]);
+      big = __builtin_fmaxf(big, __builtin_fabsf(v[it][i]));
+    }
+    bias[it] += __shfl_xor(bias[it], 1);
+    bias[it] += __shfl_xor(bias[it], 2);
   }
-  bias += __shfl_xor(bias, 1);
-  bias += __shfl_xor(bias, 2);
 #pragma unroll
   for (int o = 4; o < 64; o <<= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
   if (lane < NG) vmax[wave][lane] = big;
@@ -110,33 +114,12 @@ __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis
   for (int sl = 0; sl < NG; ++sl) {
     float mx = 0.0f;
 #pragma unroll
-    for (int w = 0; w < HB_NW; ++w) mx = __builtin_fmaxf(mx, vmax[w][K.grp[sl]]);
+    for (int w = 0; w < NW; ++w) mx = __builtin_fmaxf(mx, vmax[w][K.grp[sl]]);
     const int e = __builtin_amdgcn_readfirstlane(9 - scale_exponent(mx));
     exps[sl] = __builtin_ldexpf(1.0f, -e);
     myexp = sl == slot ? e : myexp;
   }
   const float sc = __builtin_ldexpf(1.0f, myexp);
-  if (slot >= 0) {
-    // coefficients c and c + 16 are neighbours in K: place 2 (c & 15) + (c >> 4)
-    uint32_t hi[16], lo[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) split2_f16(v[i], v[16 + i], sc, hi[i], lo[i]);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      *reinterpret_cast<u32x4*>(&vl[0][row][G * slot + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
-      *reinterpret_cast<u32x4*>(&vl[1][row][G * slot + 8 * q]) = u32x4{lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]};
-    }
-  }
-  // row of the zero-point product: slot k has elements 8k .. 8k + 5 = group-sum parts
-  // 0 0 1 0 1 2 (against z parts 0 1 0 2 1 0); elements 6, 7, 14 hold the parts of m V^T
-  // (against ones); threads of dropped groups fill the slots past the kept ones with zeros
-  uint32_t p0, p1, p2, b0, b1, b2;
-  split3(slot >= 0 ? sum : 0.0f, p0, p1, p2);
-  split3(bias, b0, b1, b2);
-  if (!(__builtin_fabsf(bias) < __builtin_inff())) {  // not finite: the first part alone (inf - inf is NaN)
-    b0 = __float_as_uint(bias) >> 16;
-    b1 = b2 = 0u;
-  }
   int rank = 0;  // dropped group: its place among the slots past the kept ones
 #pragma unroll
   for (int gg = 0; gg < NG; ++gg) {
@@ -146,8 +129,33 @@ __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis
     rank += (!kept && gg < g) ? 1 : 0;
   }
   const int ys = slot >= 0 ? slot : K.n + rank;
-  const uint32_t tail = ys == 0 ? pack2(b0, b1) : ys == 1 ? pack2(b2, 0u) : 0u;
-  *reinterpret_cast<u32x4*>(&yl[row][8 * ys]) = u32x4{pack2(p0, p0), pack2(p1, p0), pack2(p1, p2), tail};
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int row = row_of((tid >> 2) + 16 * NW * it);
+    if (slot >= 0) {
+      // coefficients c and c + 16 are neighbours in K: place 2 (c & 15) + (c >> 4)
+      uint32_t hi[16], lo[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) split2_f16(v[it][i], v[it][16 + i], sc, hi[i], lo[i]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        *reinterpret_cast<u32x4*>(&vl[0][row][G * slot + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
+        *reinterpret_cast<u32x4*>(&vl[1][row][G * slot + 8 * q]) = u32x4{lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]};
+      }
+    }
+    // row of the zero-point product: slot k has elements 8k .. 8k + 5 = group-sum parts
+    // 0 0 1 0 1 2 (against z parts 0 1 0 2 1 0); elements 6, 7, 14 hold the parts of m V^T
+    // (against ones); threads of dropped groups fill the slots past the kept ones with zeros
+    uint32_t p0, p1, p2, b0, b1, b2;
+    split3(slot >= 0 ? sum[it] : 0.0f, p0, p1, p2);
+    split3(bias[it], b0, b1, b2);
+    if (!(__builtin_fabsf(bias[it]) < __builtin_inff())) {  // not finite: the first part alone (inf - inf is NaN)
+      b0 = __float_as_uint(bias[it]) >> 16;
+      b1 = b2 = 0u;
+    }
+    const uint32_t tail = ys == 0 ? pack2(b0, b1) : ys == 1 ? pack2(b2, 0u) : 0u;
+    *reinterpret_cast<u32x4*>(&yl[row][8 * ys]) = u32x4{pack2(p0, p0), pack2(p1, p0), pack2(p1, p2), tail};
+  }
 }
 
 // The z side of that product for slot sl (< NG) of a token with metadata word m and width b

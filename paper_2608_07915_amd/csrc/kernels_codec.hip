@@ -15,6 +15,7 @@
 #include "device_common.hpp"
 #include "encode_dev.hpp"
 #include "kernels.hpp"
+#include "splits.hpp"
 
 namespace spectra_dev {
 
@@ -340,7 +341,8 @@ __global__ __launch_bounds__(256, 2) void encode_f32_kernel(EncodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Decode: a wavefront rebuilds all 128 channels of 64-token tiles (lane = token of a tile).
+// Decode: a wavefront rebuilds all 128 channels of its units, 64-token tiles (TB = 2) or
+// 32-token halves of them (lane = token of the tile either way).
 // ---------------------------------------------------------------------------
 // The basis sits in LDS as two fp16 parts per kept group, scaled by the power of two that
 // brings the group's largest entry into [2^8, 2^9). A lane turns its own token's payload
@@ -357,16 +359,19 @@ __global__ __launch_bounds__(256, 2) void encode_f32_kernel(EncodeArgs a) {
 // vector memory counter retires in order: a load behind 64 stores would wait for them).
 // Bound by the fp32 rows written: 537 MB for eight heads of 131k tokens, 106 us for stores
 // alone in this pattern. With 32 channels per wavefront, three bf16 parts and every code
-// unpacked by four wavefronts 176 us, now 128 us at 8x.
+// unpacked by four wavefronts 176 us, now 128 us at 8x. Whole tiles take all 256 registers and
+// spill 20 (44 bytes of scratch per lane), half tiles take 194.
 constexpr int DC_NW = HB_NW;  // wavefronts per workgroup
+static_assert(DC_NW == spectra::DECODE_WAVES, "wavefronts of a workgroup");
 __host__ __device__ constexpr int decode_lds_bytes() { return hb_lds_bytes(); }
 
-__global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
+template <int TB, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void decode_kernel(DecodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dsm[];
   uint16_t(*vl)[D][HB_VP] = reinterpret_cast<uint16_t(*)[D][HB_VP]>(dsm);            // [part][row][32 slot + place]
   uint16_t(*yl)[HB_YP] = reinterpret_cast<uint16_t(*)[HB_YP]>(dsm + 2 * D * HB_VP * 2);  // [row][8 slot + element]
-  __shared__ float vmax[DC_NW][NG];
-  __shared__ __attribute__((aligned(16))) float scl[DC_NW][TILE];  // a slot's scales of each wavefront's tile
+  __shared__ float vmax[NW][NG];
+  __shared__ __attribute__((aligned(16))) float scl[NW][32 * TB];  // a slot's scales of each wavefront's unit
   const int s = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -375,44 +380,48 @@ __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
   const int W = a.W;
   if (!K.ok || K.used > W) return;  // width table inconsistent with the record: write nothing
   const int64_t first_tile = a.t0 >> 6, end = a.t0 + a.n;
-  const int64_t n_tiles = ((end - 1) >> 6) - first_tile + 1;
-  const int64_t step = (int64_t)gridDim.x * DC_NW;
-  int64_t tile = (int64_t)blockIdx.x * DC_NW + wave;
+  const int64_t n_units = (((end - 1) >> 6) - first_tile + 1) * (2 / TB);
+  // half tiles spread over the workgroups before a workgroup's second wavefront takes one; a
+  // workgroup's whole tiles are neighbours (131k tokens of eight heads 127 us, spread 130)
+  const int64_t step = (int64_t)gridDim.x * NW;
+  int64_t unit = TB == 1 ? (int64_t)blockIdx.x + (int64_t)wave * gridDim.x : (int64_t)blockIdx.x * NW + wave;
 
   // this lane's token of a tile: payload words and metadata of every kept slot
   const uint32_t* rec = a.packed + (int64_t)s * a.t_cap * W + first_tile * (int64_t)(TILE * W) + lane;
   uint32_t words[NG][8], meta[NG];
-  auto load_slot = [&](int sl, int64_t tt) {
-    const uint32_t* src = rec + tt * (int64_t)(TILE * W);
+  auto load_slot = [&](int sl, int64_t u) {
+    const uint32_t* src = rec + (TB == 2 ? u : u >> 1) * (int64_t)(TILE * W);
     const int b = K.bits[sl], pay = K.pay[sl];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (i < b) words[sl][i] = src[(pay + i) * TILE];
     meta[sl] = src[sl * TILE];
   };
-  if (tile < n_tiles) {
+  if (unit < n_units) {
 #pragma unroll
     for (int sl = 0; sl < NG; ++sl)
-      if (sl < K.n) load_slot(sl, tile);
+      if (sl < K.n) load_slot(sl, unit);
   }
 
   float exps[NG];  // per slot: 2^-e of its scale 2^e
-  stage_head_basis(a.basis + (int64_t)s * D * D, a.mean + (int64_t)s * D, K, tid, vl, yl, vmax, exps,
+  stage_head_basis<NW>(a.basis + (int64_t)s * D * D, a.mean + (int64_t)s * D, K, tid, vl, yl, vmax, exps,
                    [](int ch) { return 32 * (ch & 3) + (ch >> 2); });  // column c of block b is channel 4c + b
   __syncthreads();
 
   uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
   asm volatile("" : "+v"(magic));
-  for (; tile < n_tiles; tile += step) {
-    const int64_t next = tile + step < n_tiles ? tile + step : tile;  // past the last tile: its words again
-    f32x16 out[2][4];  // [32-token block][32-channel block]
+  for (; unit < n_units; unit += step) {
+    const int64_t next = unit + step < n_units ? unit + step : unit;  // past the last unit: its words again
+    const int64_t tile = TB == 2 ? unit : unit >> 1;
+    const int blk = TB == 2 ? 0 : (int)(unit & 1);  // first 32-token block of the unit
+    f32x16 out[TB][4];  // [32-token block][32-channel block]
     // zero-point and mean terms: lane = token packs its slots' elements, the half swap makes
     // the operands of both blocks (slots 0 and 1 in K step 0, 2 and 3 in K step 1)
     u32x4 ze[NG];
 #pragma unroll
     for (int sl = 0; sl < NG; ++sl) ze[sl] = zero_elements(meta[sl], sl < K.n ? K.bits[sl] : 0, zero_tail(sl));
     {
-      bf16x8 zop[2][2];  // [K step][block]
+      bf16x8 zop[2][TB];  // [K step][block]
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         u32x4 za, zb;
@@ -422,15 +431,15 @@ __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
           za[i] = r[0];
           zb[i] = r[1];
         }
-        zop[ks][0] = as_bf16x8(za);
-        zop[ks][1] = as_bf16x8(zb);
+        zop[ks][0] = as_bf16x8(TB == 1 && blk ? zb : za);
+        if constexpr (TB == 2) zop[ks][TB - 1] = as_bf16x8(zb);
       }
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) {
         const bf16x8 y0 = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[32 * cb + col][8 * h]));
         const bf16x8 y1 = as_bf16x8(*reinterpret_cast<const u32x4*>(&yl[32 * cb + col][16 + 8 * h]));
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
+        for (int tb = 0; tb < TB; ++tb) {
           f32x16 o = {};
           if (K.n > 2) o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zop[1][tb], y1, o, 0, 0, 0);
           out[tb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zop[0][tb], y0, o, 0, 0, 0);
@@ -440,7 +449,7 @@ __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
 #pragma unroll
     for (int sl = 0; sl < NG; ++sl) {
       if (sl < K.n) {
-        f16x8 cod[2][2];  // [block][K step]
+        f16x8 cod[TB][2];  // [block][K step]
         with_bits(K.bits[sl], [&](auto bc) {
           constexpr int B = decltype(bc)::value;
           uint32_t Z[8];
@@ -456,46 +465,47 @@ __global__ __launch_bounds__(64 * DC_NW, 2) void decode_kernel(DecodeArgs a) {
               ca[i] = r[0];
               cb[i] = r[1];
             }
-            cod[0][ks] = __builtin_bit_cast(f16x8, ca);
-            cod[1][ks] = __builtin_bit_cast(f16x8, cb);
+            cod[0][ks] = __builtin_bit_cast(f16x8, TB == 1 && blk ? cb : ca);
+            if constexpr (TB == 2) cod[TB - 1][ks] = __builtin_bit_cast(f16x8, cb);
           }
         });
         // each token's scale, back from LDS for the rows of this lane's sums
-        scl[wave][lane] = h2f(meta[sl]) * exps[sl];
-        f32x4 st[2][4];
+        if (TB == 2 || h == blk) scl[wave][TB == 2 ? lane : col] = h2f(meta[sl]) * exps[sl];
+        f32x4 st[TB][4];
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
           for (int q = 0; q < 4; ++q) st[tb][q] = *reinterpret_cast<const f32x4*>(&scl[wave][32 * tb + 8 * q + 4 * h]);
         load_slot(sl, next);
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
-          f32x16 g[2] = {f32x16{}, f32x16{}};
+          f32x16 g[TB] = {};
 #pragma unroll
           for (int p = 0; p < 2; ++p)
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
               const f16x8 av = *reinterpret_cast<const f16x8*>(&vl[p][32 * cb + col][G * sl + 16 * h + 8 * ks]);
 #pragma unroll
-              for (int tb = 0; tb < 2; ++tb) g[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cod[tb][ks], av, g[tb], 0, 0, 0);
+              for (int tb = 0; tb < TB; ++tb) g[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cod[tb][ks], av, g[tb], 0, 0, 0);
             }
 #pragma unroll
-          for (int tb = 0; tb < 2; ++tb)
+          for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
             for (int i = 0; i < 16; ++i) out[tb][cb][i] = __builtin_fmaf(st[tb][i >> 2][i & 3], g[tb][i], out[tb][cb][i]);
         }
         // the sums stay here (not sunk past the next slots with all products alive)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) asm volatile("" : "+v"(out[0][cb]), "+v"(out[1][cb]));
+        for (int cb = 0; cb < 4; ++cb) asm volatile("" : "+v"(out[0][cb]), "+v"(out[TB - 1][cb]));
       }
     }
     // lane (h, col): channels 4 col .. 4 col + 3 of tokens 8q + 4h + r: every store of the
     // wavefront is two whole 512-byte rows
-    const int64_t t0 = ((first_tile + tile) << 6) + 4 * h;
+    const int64_t tu = ((first_tile + tile) << 6) + 32 * blk;
+    const int64_t t0 = tu + 4 * h;
     float* o = a.out + ((int64_t)s * a.n + (t0 - a.t0)) * D + 4 * col;
-    const bool whole = ((first_tile + tile) << 6) >= a.t0 && ((first_tile + tile) << 6) + TILE <= end;
+    const bool whole = tu >= a.t0 && tu + 32 * TB <= end;
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb)
+    for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int r = 32 * tb + 8 * (i >> 2) + (i & 3);
@@ -680,11 +690,15 @@ hipError_t launch_encode(const EncodeArgs& a, bool f32_input, hipStream_t st) {
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
   const int64_t first_tile = a.t0 >> 6, last_tile = (a.t0 + a.n - 1) >> 6;
   const int64_t n_tiles = last_tile - first_tile + 1;
-  // one round of workgroups (one per CU: LDS and registers): the basis is split once per
-  // workgroup, and each wavefront streams many tiles
-  int64_t per_stream = (256 + a.n_streams - 1) / a.n_streams;
-  if (per_stream > (n_tiles + DC_NW - 1) / DC_NW) per_stream = (n_tiles + DC_NW - 1) / DC_NW;
-  hipLaunchKernelGGL(decode_kernel, dim3((unsigned)per_stream, (unsigned)a.n_streams), dim3(64 * DC_NW), decode_lds_bytes(), st, a);
+  const DecodeGrid g = decode_grid(a.n_streams, n_tiles);
+  const dim3 grid((unsigned)g.per_stream, (unsigned)a.n_streams);
+  static_assert(2 * (decode_lds_bytes() + 4 * (NG + 32) * 4) <= 160 * 1024, "two workgroups of four wavefronts per CU");
+  if (g.half_tiles && g.waves == 4)
+    hipLaunchKernelGGL((decode_kernel<1, 4>), grid, dim3(256), decode_lds_bytes(), st, a);
+  else if (g.half_tiles)
+    hipLaunchKernelGGL((decode_kernel<1, DC_NW>), grid, dim3(64 * DC_NW), decode_lds_bytes(), st, a);
+  else
+    hipLaunchKernelGGL((decode_kernel<2, DC_NW>), grid, dim3(64 * DC_NW), decode_lds_bytes(), st, a);
   return hipGetLastError();
 }
 

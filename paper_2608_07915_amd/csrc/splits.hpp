@@ -19,6 +19,33 @@ inline Split split_tiles(int64_t n_tiles, int64_t tiles_per_chunk) {
 }
 
 // ---------------------------------------------------------------------------
+// Reconstruction of per-head records
+// ---------------------------------------------------------------------------
+constexpr int DECODE_WAVES = 8;  // wavefronts of a workgroup, each rebuilding its own units
+struct DecodeGrid {
+  int32_t per_stream;  // workgroups per stream
+  int32_t waves;       // of a workgroup
+  bool half_tiles;     // units of 32 tokens instead of 64
+};
+
+// One round of workgroups, one per CU (LDS and registers), each of which splits its stream's
+// basis once; rounded up instead (12 streams: 264 workgroups), 32000 tokens of 12 streams took
+// 60 us, now 43, of 40 streams 184, now 162. Units of 64 tokens, but of 32 as long as no
+// wavefront then has more than one: the chain through one unit sets the time of short windows
+// (eight heads at 12x: 500 tokens 13.7 us by whole tiles in one workgroup per stream, now 10.6,
+// and 12.3 with four wavefronts sharing a tile; 4000 tokens 15.0, now 12.5, and 14.3; 8192 at
+// 8x 18.3 and 17.1, beyond which halves would be a second round). Up to two tiles: a workgroup of four
+// wavefronts, of which a CU holds two (264 streams of 64 tokens: 24 us, now 16; eight streams
+// 12.8, now 11.3).
+inline DecodeGrid decode_grid(int64_t n_streams, int64_t n_tiles) {
+  if (n_tiles <= 2) return DecodeGrid{1, 4, true};
+  const int64_t n = N_CU > n_streams ? N_CU / n_streams : 1;
+  const bool half = 2 * n_tiles <= n * DECODE_WAVES;
+  const int64_t most = half ? 2 * n_tiles : ceil_div(n_tiles, DECODE_WAVES);
+  return DecodeGrid{(int32_t)(n < most ? n : most), DECODE_WAVES, half};
+}
+
+// ---------------------------------------------------------------------------
 // Workspace of the per-head attention calls, in chunks per (sequence, KV head)
 // ---------------------------------------------------------------------------
 // What one call has room for: the larger of chunks of at least 16 tiles for 768 workgroups

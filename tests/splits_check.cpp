@@ -29,6 +29,17 @@ static void covers(const char* what, int64_t g, int64_t tiles, Split s) {
 }
 
 int main() {
+  for (int64_t g : GROUPS)
+    for (int64_t tiles = 1; tiles < 5000; tiles += tiles < 300 ? 1 : 7) {
+      // one round of workgroups, none without a unit, halves only where no wavefront has two
+      const DecodeGrid d = decode_grid(g, tiles);
+      const int64_t units = d.half_tiles ? 2 * tiles : tiles, slots = d.waves == 4 ? 512 : 256;
+      CHECK(d.per_stream >= 1 && d.per_stream <= (d.half_tiles ? units : ceil_div(units, d.waves)) && (d.per_stream * g <= slots || d.per_stream == 1), "decode: %lld streams, %lld tiles: %d",
+            (long long)g, (long long)tiles, d.per_stream);
+      CHECK(!d.half_tiles || units <= (int64_t)d.per_stream * d.waves, "decode: %lld streams, %lld tiles: a second half tile", (long long)g,
+            (long long)tiles);
+      CHECK(d.waves == 8 || (d.waves == 4 && d.half_tiles), "decode: %d wavefronts", d.waves);
+    }
   for (int64_t g : GROUPS) {
     int32_t most = 0;
     for (int64_t tiles = 1; tiles < 9000; tiles += tiles < 800 ? 1 : 7) {

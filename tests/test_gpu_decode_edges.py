@@ -9,7 +9,7 @@ import pytest
 
 import paper_2608_07915_amd as S
 from gpu_parity import rel_l2
-from layer_records import make_layer_cache
+from layer_records import make_layer_cache, repeat_streams
 
 pytestmark = pytest.mark.gpu
 
@@ -38,6 +38,31 @@ def test_decode_edges(widths, T, t0, n, scale):
     got = S.spectra_decode(codec, packed, t_cap, t0, T).cpu().numpy()
     for s in range(n):
         assert rel_l2(got[s], want[s]) <= 1e-6
+
+
+LONG = [
+    # widths, tokens, first slot, streams, times over: 256 CUs of eight wavefronts in all
+    ([8, 7, 6, 5], 64 * 130 + 9, 37, 4, 10),   # 48 wavefronts per stream: two or three tiles each
+    ([1, 2, 3, 4], 64 * 130 - 3, 0, 4, 10),
+    ([0, 5, 0, 3], 64 * 60, 63, 2, 40),        # 24 per stream
+    ([3, 2, 1, 0], 64 * 11 + 1, 31, 3, 90),    # one workgroup per stream: one or two tiles
+    ([4, 2, 0, 0], 64 * 4, 0, 3, 90),          # half tiles, every wavefront one
+    ([2, 0, 1, 0], 64 * 5 - 1, 1, 3, 90),      # five tiles, more than the halves' round
+    ([6, 3, 0, 0], 64, 33, 4, 80),             # two tiles: four wavefronts, two workgroups per CU
+]
+
+
+@pytest.mark.parametrize("widths,T,t0,n,times", LONG)
+def test_decode_several_tiles_per_wavefront(widths, T, t0, n, times):
+    """Wavefronts that walk several tiles (the next tile's words in flight, scales in LDS again)
+    and some that walk one fewer, with ragged ends; grids around their limits."""
+    rng = np.random.default_rng([T, t0, n])
+    codec, packed, t_cap, want = make_layer_cache(rng, 128, widths, T, t0, n, g=32)
+    codec, packed = repeat_streams(codec, packed, times)
+    got = S.spectra_decode(codec, packed, t_cap, t0, T)
+    for s in range(n):
+        assert rel_l2(got[s].cpu().numpy(), want[s]) <= 1e-6
+        assert torch.equal(got[s::n], got[s].expand(times, T, 128))
 
 
 def test_decode_infinite_mean():
