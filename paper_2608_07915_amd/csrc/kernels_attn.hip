@@ -47,6 +47,7 @@ static_assert(KMFMA_MAX == KM_MAX, "plan sizes");
 constexpr int QA_SLOT = KM_MAX * 4 * 4;  // uint32
 constexpr int QA_QUAD = NG * QA_SLOT;
 constexpr int WAVES = 4;
+static_assert(WAVES == spectra::SCAN_WAVES, "a tile per wavefront");
 
 // ---------------------------------------------------------------------------
 // Decode-step append, done by the workgroup whose chunk holds the last tile:
@@ -791,39 +792,6 @@ size_t attention_call_bytes(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads
   return attention_partial_floats(batch, n_q_heads, attention_max_chunks((int64_t)batch * n_kv_heads, (n_tokens + 63) / 64)) * sizeof(float);
 }
 
-// Split of each (sequence, kv head) token range into chunks of whole tiles for a card that
-// holds `slots` of the scan's workgroups at once: as many chunks as fill those slots, of at
-// least MIN_TILES tiles (two per wavefront), small ones of whole rounds of the four
-// wavefronts. A few workgroups beyond the slots start when the others end and nearly double
-// the scan's time (32k tokens at 4x, 512 slots: 520 workgroups 33.5 us, 352 workgroups 26.5),
-// so the count is rounded down, over the fewest rounds of workgroups that come out 85% full.
-// The last tile is a chunk of its own (in a decode step its workgroup also appends the new
-// token), inside the slots when the slot that it takes costs the other chunks less than one
-// tile per wavefront, otherwise queued behind them.
-// Calls, against chunks of at least 16 tiles for 768 workgroups: 32k tokens at 4x 35.2 ->
-// 31.5 us, seven heads over 65k tokens 34.2 -> 30.9, 1000 tokens 23.8 -> 22.8; equal at 131k
-// tokens (38.5 and 38.2). Chunks of four tiles are no faster at 1000 tokens and 2.5 us slower
-// at 16k (every workgroup prepares the queries).
-constexpr int MIN_TILES = 8;
-static void split_chunks(AttnArgs& a, int slots) {
-  const int64_t body = (a.n_tokens + 63) / 64 - 1;
-  const int64_t groups = (int64_t)a.batch * a.n_kv_heads;
-  int64_t n = 0;
-  for (int64_t rounds = 1; rounds <= 4; ++rounds) {
-    n = rounds * slots / groups;
-    if (n * groups * 100 >= 85 * rounds * slots) break;
-  }
-  if (n > 1 && body < WAVES * n * n) --n;
-  const int64_t cap = attention_max_chunks(groups, body + 1) - 1, most = (body + MIN_TILES - 1) / MIN_TILES;
-  if (n > cap) n = cap;
-  if (n > most) n = most;
-  if (n < 1) n = body > 0 ? 1 : 0;
-  int64_t tpc = n > 0 ? (body + n - 1) / n : 1;
-  if (tpc < 16) tpc = (tpc + WAVES - 1) / WAVES * WAVES;
-  a.tiles_per_chunk = (int32_t)tpc;
-  a.n_chunks = (int32_t)((body + tpc - 1) / tpc) + 1;
-}
-
 template <int NQ, int PK, int PV, bool EXACT>
 static int32_t launch_nq_pw(const AttnArgs& a, hipStream_t st) {
   const int wpw = PK > 0 ? PK + PV : a.Wk + a.Wv;
@@ -834,12 +802,16 @@ static int32_t launch_nq_pw(const AttnArgs& a, hipStream_t st) {
   if (a.app_k && (size_t)append_stage_bytes(a.app_f32 != 0) > lds) lds = append_stage_bytes(a.app_f32 != 0);
   // more (sequence, kv head) groups than XCDs: chunks of a group kept on one XCD
   AttnArgs g = a;
-  g.group_major = a.n_kv_heads * a.batch > 8 ? 1 : 0;
+  const int64_t groups = (int64_t)a.n_kv_heads * a.batch;
+  g.group_major = groups > 8 ? 1 : 0;
   // workgroups a CU holds: three wavefronts per SIMD by the registers of the shapes with one
   // head quad and at most 24 prefetched words, two for the others; and its 160 KB of LDS
   constexpr int REGS = NQ == 1 && PK + PV <= 24 ? 3 : 2;
   const int fit = (int)(160 * 1024 / (lds + attn_static_lds(NQ)));
-  split_chunks(g, 256 * (fit < 1 ? 1 : fit < REGS ? fit : REGS));
+  const Split split = scan_split(groups, (a.n_tokens + 63) / 64, fit < 1 ? 1 : fit < REGS ? fit : REGS, NQ * (a.Wk + a.Wv),
+                                 a.app_k != nullptr, a.max_chunks);
+  g.tiles_per_chunk = split.tiles_per_chunk;
+  g.n_chunks = split.n_chunks;
   const dim3 grid = g.group_major ? dim3(g.n_chunks * a.n_kv_heads * a.batch, 1, 1) : dim3(g.n_chunks, a.n_kv_heads, a.batch);
   hipLaunchKernelGGL((attn_kernel<NQ, PK, PV, EXACT>), grid, dim3(256), lds, st, g);
   return g.n_chunks;

@@ -15,7 +15,7 @@ CSRC = os.path.join(ROOT, "paper_2608_07915_amd", "csrc")
 def test_grid_splits():
     with tempfile.TemporaryDirectory() as d:
         exe = os.path.join(d, "splits_check")
-        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", f"-I{CSRC}",
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover", f"-I{CSRC}",
                         os.path.join(ROOT, "tests", "splits_check.cpp"), "-o", exe], check=True)
         r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.strip() == "OK", r.stdout + r.stderr
