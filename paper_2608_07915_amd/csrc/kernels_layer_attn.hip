@@ -24,6 +24,7 @@
 #include "attn_common.hpp"
 #include "layer.hpp"
 #include "layer_codes.hpp"
+#include "splits.hpp"
 
 namespace spectra_dev {
 
@@ -495,7 +496,7 @@ __global__ __launch_bounds__(512, 4) void layer_values_kernel(LayerAttnArgs a) {
 // needed); grid (heads, sequences, d / 64 groups). The softmax maximum over the
 // score chunks and the weights' sum over the value chunks are taken by every workgroup itself (one maximum per chunk).
 // ---------------------------------------------------------------------------
-constexpr int LA_CHUNKS = 256;  // score chunks per sequence (at most)
+constexpr int LA_CHUNKS = spectra::N_CU;  // score chunks per sequence (at most)
 
 __global__ __launch_bounds__(256) void layer_combine_kernel(LayerAttnArgs a) {
   // thread -> (coefficient 64 z + (tid & 63), every fourth chunk from tid >> 6): four short
@@ -598,32 +599,18 @@ __global__ __launch_bounds__(256) void layer_rotate_kernel(LayerAttnArgs a) {
 namespace spectra {
 using namespace spectra_dev;
 
-// About 256 score workgroups over all sequences (one per CU: LDS), at least two tiles per chunk.
-constexpr int LA_MIN_TILES = 2;
-static int64_t layer_chunks_wanted(int32_t batch) { return (LA_CHUNKS + batch - 1) / batch; }
-static int32_t layer_attention_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk) {
-  const int64_t n_tiles = (n_tokens + 63) / 64;
-  const int64_t want = layer_chunks_wanted(batch);
-  int64_t tpc = (n_tiles + want - 1) / want;
-  if (tpc < LA_MIN_TILES) tpc = LA_MIN_TILES;
-  *tiles_per_chunk = (int32_t)tpc;
-  return (int32_t)((n_tiles + tpc - 1) / tpc);
-}
-
 // Value pass: two score chunks per workgroup and head block, so its softmax reference is
 // the larger of their two maxima.
 static int32_t layer_value_chunks(int32_t batch, int64_t n_tokens, int32_t* tiles_per_chunk) {
-  int32_t tpc;
-  const int32_t nch = layer_attention_chunks(batch, n_tokens, &tpc);
-  *tiles_per_chunk = 2 * tpc;
-  return (nch + 1) / 2;
+  const Split s = layer_score_split(batch, (n_tokens + 63) / 64);
+  *tiles_per_chunk = 2 * s.tiles_per_chunk;
+  return (s.n_chunks + 1) / 2;
 }
 
 // Sized for the most chunks that any token count up to n_tokens is split into, so a workspace
 // taken for a longer cache serves every shorter one.
 size_t layer_attention_ws_floats(int32_t batch, int32_t n_q_heads, int32_t d, int64_t n_tokens) {
-  const int64_t n_tiles = (n_tokens + 63) / 64, want = layer_chunks_wanted(batch);
-  const int64_t most = (n_tiles + LA_MIN_TILES - 1) / LA_MIN_TILES, nch = most < want ? most : want, nv = (nch + 1) / 2;
+  const int64_t n_tiles = (n_tokens + 63) / 64, nch = layer_score_chunks(batch, n_tiles), nv = (nch + 1) / 2;
   const int64_t B = batch, H = n_q_heads;
   auto r64 = [](int64_t n) { return (n + 63) / 64 * 64; };  // 256-byte aligned sections
   return (size_t)(r64(B * H * d) + r64(B * LA_H * d) + r64(B * H * 16) + r64(B * H * n_tiles * 64) + r64(B * nch * H) +
@@ -631,7 +618,9 @@ size_t layer_attention_ws_floats(int32_t batch, int32_t n_q_heads, int32_t d, in
 }
 
 void layer_attention_ws_layout(LayerAttnArgs& a, float* ws) {
-  a.n_chunks = layer_attention_chunks(a.batch, a.n_tokens, &a.tiles_per_chunk);
+  const Split s = layer_score_split(a.batch, (a.n_tokens + 63) / 64);
+  a.n_chunks = s.n_chunks;
+  a.tiles_per_chunk = s.tiles_per_chunk;
   a.nv_chunks = layer_value_chunks(a.batch, a.n_tokens, &a.v_tiles_per_chunk);
   const int64_t B = a.batch, H = a.n_q_heads;
   auto r64 = [](int64_t n) { return (n + 63) / 64 * 64; };

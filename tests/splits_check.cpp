@@ -41,6 +41,15 @@ int main() {
       CHECK(d.waves == 8 || (d.waves == 4 && d.half_tiles), "decode: %d wavefronts", d.waves);
     }
   for (int64_t g : GROUPS) {
+    int64_t layer_most = 0;
+    for (int64_t tiles = 1; tiles < 9000; tiles += tiles < 800 ? 1 : 7) {
+      const Split l = layer_score_split(g, tiles);
+      const int64_t room = layer_score_chunks(g, tiles);
+      covers("per layer", g, tiles, l);
+      CHECK(l.n_chunks <= room && room >= layer_most && room <= 256 && (g > 256 || l.n_chunks * g <= 256),
+            "per layer: %lld sequences, %lld tiles: %d chunks, room for %lld", (long long)g, (long long)tiles, l.n_chunks, (long long)room);
+      layer_most = room;
+    }
     int32_t most = 0;
     for (int64_t tiles = 1; tiles < 9000; tiles += tiles < 800 ? 1 : 7) {
       const int32_t cap = attention_max_chunks(g, tiles), ws = attention_workspace_chunks(g, tiles);
