@@ -21,6 +21,7 @@
 #include "kernels.hpp"
 #include "layer.hpp"
 #include "layer_codes.hpp"
+#include "splits.hpp"
 
 namespace spectra_dev {
 
@@ -678,10 +679,8 @@ hipError_t launch_layer_encode(const LayerEncodeArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_layer_decode(const LayerDecodeArgs& a, hipStream_t st) {
-  // one workgroup per CU (LDS): every workgroup walks as many ranges as the longest
-  const int64_t ranges = (a.n + LD_TOK - 1) / LD_TOK, nb = a.d / LD_CH;
-  const int64_t each = (ranges * nb * a.n_streams + 255) / 256;
-  const dim3 grid((unsigned)((ranges + each - 1) / each * nb), 1, a.n_streams);
+  const int64_t nb = a.d / LD_CH;
+  const dim3 grid((unsigned)(layer_decode_split((a.n + LD_TOK - 1) / LD_TOK, nb * a.n_streams) * nb), 1, a.n_streams);
   if (a.lscale)
     hipLaunchKernelGGL(layer_decode_kernel<true>, grid, dim3(64 * LD_NW), 0, st, a);
   else

@@ -40,6 +40,12 @@ int main() {
             (long long)tiles);
       CHECK(d.waves == 8 || (d.waves == 4 && d.half_tiles), "decode: %d wavefronts", d.waves);
     }
+  for (int64_t g : GROUPS)
+    for (int64_t ranges = 1; ranges < 3000; ++ranges) {
+      const int64_t n = layer_decode_split(ranges, g);
+      CHECK(n >= 1 && n <= ranges && (n * g <= 256 || n == 1) && (n == 1 || ceil_div(ranges, n - 1) > ceil_div(ranges, n)),
+            "per-layer rows: %lld blocks, %lld ranges: %lld", (long long)g, (long long)ranges, (long long)n);
+    }
   for (int64_t g : GROUPS) {
     int64_t layer_most = 0;
     for (int64_t tiles = 1; tiles < 9000; tiles += tiles < 800 ? 1 : 7) {
