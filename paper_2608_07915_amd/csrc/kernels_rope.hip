@@ -59,7 +59,8 @@ __host__ __device__ constexpr int rope_lds_bytes(int nh) { return rope_off_wt(nh
 static_assert(rope_off_kmeta() % 16 == 0 && rope_off_kh() % 16 == 0 && rope_off_qpp(4) % 16 == 0, "16-byte reads");
 static_assert(rope_off_wt(4) % 16 == 0 && (WROW * 2) % 16 == 0, "weight rows are read 16 bytes at a time");
 static_assert(2 * (2 * 4) * AROW * 4 <= D * RKROW * 4, "value sums of both token halves reuse the key rows");
-static_assert(rope_lds_bytes(4) <= 160 * 1024 && rope_lds_bytes(8) <= 160 * 1024, "LDS of one CU");
+__host__ __device__ constexpr int rope_static_lds(int nh) { return nh * (2 + NG) * 4; }  // what the kernel declares itself
+static_assert(rope_lds_bytes(4) + rope_static_lds(4) <= 160 * 1024 && rope_lds_bytes(8) + rope_static_lds(8) <= 160 * 1024, "LDS of one CU");
 static_assert(rope_off_qpp(8) % 16 == 0 && rope_off_wt(8) % 16 == 0, "16-byte reads");
 
 // cos and sin of an angle given exactly in fp64 (a position below 2^28 times an
@@ -535,7 +536,8 @@ __host__ __device__ constexpr int r4_off_wt(int nh) { return r4_off_red(nh) + 4 
 __host__ __device__ constexpr int r4_lds_bytes(int nh) { return r4_off_wt(nh) + 4 * 2 * nh * WROW * 2; }
 static_assert(r4_off_codes() % 16 == 0 && r4_off_kmeta() % 16 == 0 && r4_off_tab() % 16 == 0, "16-byte reads");
 static_assert(r4_off_vsum() % 16 == 0 && r4_off_qpp(8) % 16 == 0 && r4_off_wt(8) % 16 == 0, "16-byte reads");
-static_assert(2 * r4_lds_bytes(8) <= 160 * 1024, "two workgroups per CU");
+__host__ __device__ constexpr int r4_static_lds(int nh) { return nh * (1 + NG) * 4; }  // what the kernel declares itself
+static_assert(2 * (r4_lds_bytes(8) + r4_static_lds(8)) <= 160 * 1024, "two workgroups per CU");
 static_assert(16 * AROW * 4 <= RTT * RCP * 2, "the value sums of the merge fit the code rows");
 
 __global__ __launch_bounds__(R4T, 2) void rope_attn4_kernel(AttnArgs a) {
@@ -959,7 +961,9 @@ __host__ __device__ constexpr int rw_wave_bytes(int nh, int pw) { return rw_quer
 __host__ __device__ constexpr int rw_lds_bytes(int nh, int pw) { return rw_off_wave(nh) + RW_NW * rw_wave_bytes(nh, pw); }
 static_assert(rw_off_tab() % 16 == 0 && rw_off_turn() % 16 == 0 && rw_off_qs() % 16 == 0 && rw_off_wave(4) % 16 == 0 && rw_off_wave(8) % 16 == 0, "16-byte reads");
 static_assert(rw_query_bytes(4) % 16 == 0 && rw_query_bytes(8) % 16 == 0, "16-byte reads");
-static_assert(rw_lds_bytes(4, 16) <= 160 * 1024 - 1024 && rw_lds_bytes(8, 8) <= 160 * 1024 - 1024, "LDS of one CU");
+// what the kernel declares itself: group maxima, merge states
+__host__ __device__ constexpr int rw_static_lds(int nh) { return RW_NW * (NG + 2 * nh + nh * NG) * 4; }
+static_assert(rw_lds_bytes(4, 16) + rw_static_lds(4) <= 160 * 1024 && rw_lds_bytes(8, 8) + rw_static_lds(8) <= 160 * 1024, "LDS of one CU");
 static_assert(RW_NW * 16 * AROW * 4 <= hb_lds_bytes() && RW_NW * 8 * AROW * 4 <= hb_lds_bytes(), "the merge reuses the basis rows");
 
 // Registers 0 .. (B + 1) / 2 - 1 of the joined halves Z (codes j and j + 16) from code 8h on.
@@ -1353,7 +1357,10 @@ hipError_t launch_attention_rope(const AttnArgs& a, hipStream_t st) {
   const RopeSplit rs = rope_split((int64_t)a.batch * a.n_kv_heads, a.n_qh, w, (a.n_tokens + 63) / 64);
   const bool by_wave = rs.kernel == RopeKernel::WAVE, four = rs.kernel == RopeKernel::FOUR;
   // the tile buffers need more than 64 KB of LDS: refuse a device that has less
-  if (lds < (by_wave ? rw_lds_bytes(nh, w <= 8 ? 8 : 16) : four ? r4_lds_bytes(nh) : rope_lds_bytes(nh))) return hipErrorInvalidConfiguration;
+  const int need = by_wave ? rw_lds_bytes(nh, w <= 8 ? 8 : 16) + rw_static_lds(nh)
+                   : four  ? r4_lds_bytes(nh) + r4_static_lds(nh)
+                           : rope_lds_bytes(nh) + rope_static_lds(nh);
+  if (lds < need) return hipErrorInvalidConfiguration;
   AttnArgs g = a;
   g.n_chunks = rs.split.n_chunks;
   g.tiles_per_chunk = rs.split.tiles_per_chunk;
