@@ -52,6 +52,13 @@ __device__ __forceinline__ int scale_exponent(float v) {
   return e < -100 ? -100 : (e > 100 ? 100 : e);
 }
 
+// Of a row whose largest entry is v: the exponent that it is scaled by, within 24 of 0 (so that
+// sums and means in its scale stay finite).
+__device__ __forceinline__ int row_exponent(float v) {
+  const int e = v > 0.0f ? scale_exponent(v) : 0;
+  return e < -24 ? -24 : (e > 24 ? 24 : e);
+}
+
 // Two fp32 values times sc as fp16 parts: x sc = hi + lo, 22 significant bits.
 __device__ __forceinline__ void split2_f16(float x0, float x1, float sc, uint32_t& hi, uint32_t& lo) {
   const f32x2 x = f32x2{x0 * sc, x1 * sc};
@@ -63,7 +70,11 @@ __device__ __forceinline__ void split2_f16(float x0, float x1, float sc, uint32_
 // ---------------------------------------------------------------------------
 // Basis of one KV head in LDS for a workgroup of NW (eight or four) wavefronts: row row_of(ch) of vl
 // holds channel ch's entries of the kept groups as two fp16 parts, group slot sl scaled by
-// the power of two that brings its largest entry into [2^8, 2^9) (exps[sl] is the inverse),
+// the power of two that brings its largest entry into [2^8, 2^9) (exps[sl] is the inverse).
+// With rscale, the row's entries, group sums and m V^T are first scaled by a power of two that
+// brings its own largest entry near 1, and rscale[row] is the inverse: channels much weaker
+// than a group's strongest keep their 22 bits (the second part ends 2^-34 below the group's
+// largest entry; channels 10^5 times weaker came out with 5e-6 of error instead of 2e-7).
 // coefficient c of a group at place 2 (c & 15) + (c >> 4). The same row of yl is the other
 // operand of one product (K = 32, bf16) that gives a token's zero-point and mean terms,
 // sum_sl zc_sl sum_j V[ch][j] + (m V^T)[ch]: slot sl has elements 8 sl .. 8 sl + 5 = parts 0 0 1
@@ -78,11 +89,14 @@ __host__ __device__ constexpr int hb_lds_bytes() { return (2 * D * HB_VP + D * H
 template <int NW = HB_NW, typename RowFn>
 __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis, const float* __restrict__ mean, const Kept& K,
                                                  int tid, uint16_t (*vl)[D][HB_VP], uint16_t (*yl)[HB_YP],
-                                                 float (*vmax)[NG], float (&exps)[NG], RowFn&& row_of) {
+                                                 float (*vmax)[NG], float (&exps)[NG], float* rscale, RowFn&& row_of) {
   constexpr int IT = HB_NW / NW;  // channels per thread
   const int wave = tid >> 6, lane = tid & 63;
   const int g = tid & 3;
-  float v[IT][32], sum[IT], bias[IT], big = 0.0f;
+  float v[IT][32], sum[IT], bias[IT], rsc[IT], big = 0.0f;
+  int slot = -1;  // kept slot of group g
+#pragma unroll
+  for (int sl = 0; sl < NG; ++sl) slot = (sl < K.n && K.grp[sl] == g) ? sl : slot;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const float* vr = basis + (int64_t)((tid >> 2) + 16 * NW * it) * D + G * g;
@@ -93,21 +107,28 @@ __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis
 #pragma unroll
     for (int i = 0; i < 32; ++i) m[i] = mr[i];
     sum[it] = bias[it] = 0.0f;
+    float most = 0.0f;
 #pragma unroll
     for (int i = 0; i < 32; ++i) {
       sum[it] += v[it][i];
       bias[it] = __builtin_fmaf(m[i], v[it][i], bias[it]);
-      big = __builtin_fmaxf(big, __builtin_fabsf(v[it][i]));
+      most = __builtin_fmaxf(most, __builtin_fabsf(v[it][i]));
     }
     bias[it] += __shfl_xor(bias[it], 1);
     bias[it] += __shfl_xor(bias[it], 2);
+    rsc[it] = 1.0f;
+    if (rscale != nullptr) {
+      float rmax = slot >= 0 ? most : 0.0f;
+      rmax = __builtin_fmaxf(rmax, __shfl_xor(rmax, 1));
+      rmax = __builtin_fmaxf(rmax, __shfl_xor(rmax, 2));
+      rsc[it] = __builtin_ldexpf(1.0f, -row_exponent(rmax));
+      if (g == 0) rscale[row_of((tid >> 2) + 16 * NW * it)] = 1.0f / rsc[it];
+    }
+    big = __builtin_fmaxf(big, most * rsc[it]);
   }
 #pragma unroll
   for (int o = 4; o < 64; o <<= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
   if (lane < NG) vmax[wave][lane] = big;
-  int slot = -1;  // kept slot of group g
-#pragma unroll
-  for (int sl = 0; sl < NG; ++sl) slot = (sl < K.n && K.grp[sl] == g) ? sl : slot;
   __syncthreads();
   int myexp = 0;
 #pragma unroll
@@ -136,7 +157,7 @@ __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis
       // coefficients c and c + 16 are neighbours in K: place 2 (c & 15) + (c >> 4)
       uint32_t hi[16], lo[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) split2_f16(v[it][i], v[it][16 + i], sc, hi[i], lo[i]);
+      for (int i = 0; i < 16; ++i) split2_f16(v[it][i], v[it][16 + i], sc * rsc[it], hi[i], lo[i]);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         *reinterpret_cast<u32x4*>(&vl[0][row][G * slot + 8 * q]) = u32x4{hi[4 * q], hi[4 * q + 1], hi[4 * q + 2], hi[4 * q + 3]};
@@ -147,10 +168,11 @@ __device__ __forceinline__ void stage_head_basis(const float* __restrict__ basis
     // 0 0 1 0 1 2 (against z parts 0 1 0 2 1 0); elements 6, 7, 14 hold the parts of m V^T
     // (against ones); threads of dropped groups fill the slots past the kept ones with zeros
     uint32_t p0, p1, p2, b0, b1, b2;
-    split3(slot >= 0 ? sum[it] : 0.0f, p0, p1, p2);
-    split3(bias[it], b0, b1, b2);
-    if (!(__builtin_fabsf(bias[it]) < __builtin_inff())) {  // not finite: the first part alone (inf - inf is NaN)
-      b0 = __float_as_uint(bias[it]) >> 16;
+    split3(slot >= 0 ? sum[it] * rsc[it] : 0.0f, p0, p1, p2);
+    const float mv = bias[it] * rsc[it];
+    split3(mv, b0, b1, b2);
+    if (!(__builtin_fabsf(mv) < __builtin_inff())) {  // not finite: the first part alone (inf - inf is NaN)
+      b0 = __float_as_uint(mv) >> 16;
       b1 = b2 = 0u;
     }
     const uint32_t tail = ys == 0 ? pack2(b0, b1) : ys == 1 ? pack2(b2, 0u) : 0u;

@@ -371,6 +371,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_kernel(DecodeArgs a) {
   uint16_t(*vl)[D][HB_VP] = reinterpret_cast<uint16_t(*)[D][HB_VP]>(dsm);            // [part][row][32 slot + place]
   uint16_t(*yl)[HB_YP] = reinterpret_cast<uint16_t(*)[HB_YP]>(dsm + 2 * D * HB_VP * 2);  // [row][8 slot + element]
   __shared__ float vmax[NW][NG];
+  __shared__ float rscale[D];  // of each row of vl: the inverse of its scale
   __shared__ __attribute__((aligned(16))) float scl[NW][32 * TB];  // a slot's scales of each wavefront's unit
   const int s = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -405,7 +406,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_kernel(DecodeArgs a) {
 
   float exps[NG];  // per slot: 2^-e of its scale 2^e
   stage_head_basis<NW>(a.basis + (int64_t)s * D * D, a.mean + (int64_t)s * D, K, tid, vl, yl, vmax, exps,
-                   [](int ch) { return 32 * (ch & 3) + (ch >> 2); });  // column c of block b is channel 4c + b
+                       rscale, [](int ch) { return 32 * (ch & 3) + (ch >> 2); });  // column c of block b is channel 4c + b
   __syncthreads();
 
   uint32_t magic = 0x64006400u;  // exponent of 1024 in both halves, in a VGPR
@@ -504,13 +505,16 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_kernel(DecodeArgs a) {
     const int64_t t0 = tu + 4 * h;
     float* o = a.out + ((int64_t)s * a.n + (t0 - a.t0)) * D + 4 * col;
     const bool whole = tu >= a.t0 && tu + 32 * TB <= end;
+    float rs[4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) rs[cb] = rscale[32 * cb + col];
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int r = 32 * tb + 8 * (i >> 2) + (i & 3);
         if (whole || (t0 + r >= a.t0 && t0 + r < end))
-          *reinterpret_cast<f32x4*>(o + r * D) = f32x4{out[tb][0][i], out[tb][1][i], out[tb][2][i], out[tb][3][i]};
+          *reinterpret_cast<f32x4*>(o + r * D) = f32x4{out[tb][0][i] * rs[0], out[tb][1][i] * rs[1], out[tb][2][i] * rs[2], out[tb][3][i] * rs[3]};
       }
   }
 }
@@ -692,7 +696,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
   const int64_t n_tiles = last_tile - first_tile + 1;
   const DecodeGrid g = decode_grid(a.n_streams, n_tiles);
   const dim3 grid((unsigned)g.per_stream, (unsigned)a.n_streams);
-  static_assert(2 * (decode_lds_bytes() + 4 * (NG + 32) * 4) <= 160 * 1024, "two workgroups of four wavefronts per CU");
+  static_assert(2 * (decode_lds_bytes() + (4 * (NG + 32) + D) * 4) <= 160 * 1024, "two workgroups of four wavefronts per CU");
   if (g.half_tiles && g.waves == 4)
     hipLaunchKernelGGL((decode_kernel<1, 4>), grid, dim3(256), decode_lds_bytes(), st, a);
   else if (g.half_tiles)

@@ -326,8 +326,9 @@ __global__ __launch_bounds__(512, 4) void layer_encode_kernel(LayerEncodeArgs a)
 // ---------------------------------------------------------------------------
 // One workgroup: 128 output channels, walking ranges of 256 tokens (wavefront w: 32 tokens x
 // all 128 channels). What depends on the channels alone is computed once per workgroup:
-// m V^T, the sums of the basis entries of each kept group and the power of two that brings
-// a group's largest entry into [2^8, 2^9). Then, per kept group of a range, the 128 x 64
+// m V^T, the sums of the basis entries of each kept group, a power of two per channel that
+// brings its largest entry near 1 and then one per group that brings its largest into [2^8, 2^9)
+// (channels far weaker than a group's strongest keep their 22 bits). Then, per kept group of a range, the 128 x 64
 // basis block goes to LDS as two fp16 parts (two buffers: the next block is split while
 // this one is multiplied) and each lane turns its token's payload words into operands in
 // registers:
@@ -371,9 +372,12 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
   __shared__ __attribute__((aligned(16))) float scl[LD_TOK];               // scales of the slot at hand
   __shared__ __attribute__((aligned(16))) float bias[LD_CH];
   __shared__ __attribute__((aligned(16))) float mean[1024];
-  __shared__ float vmax[16][LD_NW];
+  __shared__ __attribute__((aligned(16))) float rscale[LD_CH];  // of each channel: the inverse of its row's scale
   __shared__ int vexp[16];
   __shared__ LayerTable tab;
+  // largest entry of each channel in a kept group; the basis blocks take its place afterwards
+  float(*vmax)[LD_CH] = reinterpret_cast<float(*)[LD_CH]>(vl);
+  static_assert(16 * LD_CH * sizeof(float) <= sizeof(vl), "maxima fit the basis blocks");
   const int s = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -412,8 +416,9 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
       for (int i = 0; i < 16; ++i) x[i] *= 1.0f / f[16 * (i >> 3) + (i & 7)];
     }
   };
+  float rsc;  // this row's scale
   {
-    float bsum = 0.0f, x[2][16];
+    float bsum = 0.0f, rmax = 0.0f, x[2][16];
     load_v(__builtin_amdgcn_readfirstlane(tab.grp[0]), x[0]);
     for (int k0 = 0; k0 < ng; k0 += 2) {  // d is a multiple of 128: an even number of groups
 #pragma unroll
@@ -436,21 +441,28 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
           uint32_t p0, p1, p2;
           split3(sum, p0, p1, p2);
           if (sub < 3) yl[sub][row][k] = (uint16_t)(sub == 0 ? p0 : sub == 1 ? p1 : p2);
-          m = wave_max_all(m);
-          if (lane == 0) vmax[k][wave] = m;
+          m = __builtin_fmaxf(m, __shfl_xor(m, 1));
+          m = __builtin_fmaxf(m, __shfl_xor(m, 2));
+          if (sub == 0) vmax[k][ch] = m;
+          rmax = __builtin_fmaxf(rmax, m);
         }
       }
     }
     bsum += __shfl_xor(bsum, 1);
     bsum += __shfl_xor(bsum, 2);
-    if (sub == 0) bias[ch] = bsum;
+    rsc = __builtin_ldexpf(1.0f, -row_exponent(rmax));
+    if (sub == 0) {
+      bias[ch] = bsum;
+      rscale[ch] = 1.0f / rsc;
+    }
   }
   __syncthreads();
-  if (tid < n_kept) {
-    float m = vmax[tid][0];
+  // every row is scaled to a largest entry near 1 and then every group to one in [2^8, 2^9)
 #pragma unroll
-    for (int w = 1; w < LD_NW; ++w) m = __builtin_fmaxf(m, vmax[tid][w]);
-    vexp[tid] = 9 - scale_exponent(m);
+  for (int u = 0; u < 16 / LD_NW; ++u) {
+    const int k = wave + LD_NW * u;
+    const float m = wave_max_all(__builtin_fmaxf(vmax[k][lane] / rscale[lane], vmax[k][64 + lane] / rscale[64 + lane]));
+    if (lane == 0) vexp[k] = 9 - scale_exponent(m);  // read for kept slots only
   }
   __syncthreads();
 
@@ -462,7 +474,7 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
 
   // the group in v to buffer buf as two fp16 parts
   auto split_v = [&](int slot, int buf) {
-    const float sc = __builtin_ldexpf(1.0f, of_slot(slot_exp, slot));
+    const float sc = __builtin_ldexpf(rsc, of_slot(slot_exp, slot));
     uint32_t hi[8], lo[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {  // coefficients c0 + i and c0 + 16 + i are neighbours in K
@@ -623,7 +635,7 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
     }
     // lane (h, col): channels 4 col .. 4 col + 3 of tokens 8q + 4h + r: a store of the
     // wavefront is two whole 512-byte row pieces
-    const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias[4 * col]);
+    const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias[4 * col]), rs = *reinterpret_cast<const f32x4*>(&rscale[4 * col]);
     const int64_t i0 = range * LD_TOK + tw + 4 * h;
     float* o = a.out + ((int64_t)s * a.n + i0) * d + ch0 + 4 * col;
     const bool whole = range * LD_TOK + tw + 32 <= a.n;
@@ -632,7 +644,8 @@ __global__ __launch_bounds__(64 * LD_NW, 2) void layer_decode_kernel(LayerDecode
       const int r = 8 * (i >> 2) + (i & 3);
       if (whole || i0 + r < a.n)
         *reinterpret_cast<f32x4*>(o + (int64_t)r * d) =
-            f32x4{(out[0][i] + y[0][i]) + b4[0], (out[1][i] + y[1][i]) + b4[1], (out[2][i] + y[2][i]) + b4[2], (out[3][i] + y[3][i]) + b4[3]};
+            f32x4{__builtin_fmaf(out[0][i], rs[0], y[0][i]) + b4[0], __builtin_fmaf(out[1][i], rs[1], y[1][i]) + b4[1],
+                  __builtin_fmaf(out[2][i], rs[2], y[2][i]) + b4[2], __builtin_fmaf(out[3][i], rs[3], y[3][i]) + b4[3]};
     }
   }
 }

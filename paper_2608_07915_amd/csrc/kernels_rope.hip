@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(64 * RW_NW, 2) void rope_attn_wave_kernel(AttnArgs 
     qs[e] = q * a.scale_log2;
   }
   float exps[NG];
-  stage_head_basis(a.basis_k + (int64_t)s * D * D, a.mean_k + (int64_t)s * D, Kk, tid, vl, yl, vmax, exps, [](int ch) { return ch; });
+  stage_head_basis(a.basis_k + (int64_t)s * D * D, a.mean_k + (int64_t)s * D, Kk, tid, vl, yl, vmax, exps, nullptr, [](int ch) { return ch; });
   __syncthreads();
 
   float m_run[NH], l_run[NH], zacc[NH][NG];

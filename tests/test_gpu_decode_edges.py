@@ -75,3 +75,16 @@ def test_decode_infinite_mean():
     sign = np.sign(codec.basis[0, :, 40].cpu().numpy())
     assert np.array_equal(got[0], np.broadcast_to(sign * np.inf, (70, 128)))
     assert rel_l2(got[1], want[1]) <= 1e-6
+
+
+@pytest.mark.parametrize("weak", [2.0 ** -10, 2.0 ** -17, 2.0 ** -23])
+def test_decode_weak_channels(weak):
+    """Channels whose basis entries are far smaller than the others' are rebuilt to the same
+    relative precision (the bar above holds for them alone: their entries have 22 bits too)."""
+    rng = np.random.default_rng(11)
+    codec, packed, t_cap, want = make_layer_cache(rng, 128, [4, 2, 0, 1], 300, 0, 2, g=32)
+    codec.basis[:, 5:40] *= weak
+    got = S.spectra_decode(codec, packed, t_cap, 0, 300).cpu().numpy()
+    for s in range(2):
+        assert rel_l2(got[s][:, 5:40], want[s][:, 5:40] * weak) <= 1e-6
+        assert rel_l2(got[s][:, 40:], want[s][:, 40:]) <= 1e-6

@@ -37,3 +37,17 @@ def test_layer_decode_edges(d, widths, T, t0, n, scale, split):
     got = S.spectra_decode(codec, packed, t_cap, t0, T).cpu().numpy()
     for s in range(n):
         assert rel_l2(got[s], want[s]) <= 1e-6
+
+
+@pytest.mark.parametrize("weak", [2.0 ** -10, 2.0 ** -17, 2.0 ** -23])
+@pytest.mark.parametrize("split", [False, True])
+def test_layer_decode_weak_channels(split, weak):
+    """Channels whose basis entries are far smaller than the others' are rebuilt to the same
+    relative precision (the bar above holds for them alone: their entries have 22 bits too)."""
+    rng = np.random.default_rng(11)
+    codec, packed, t_cap, want = make_layer_cache(rng, 512, [4, 2, 1, 0, 3, 0, 0, 1], 300, 0, 2, split=split)
+    codec.basis[:, 5:40] *= weak
+    got = S.spectra_decode(codec, packed, t_cap, 0, 300).cpu().numpy()
+    for s in range(2):
+        assert rel_l2(got[s][:, 5:40], want[s][:, 5:40] * weak) <= 1e-6
+        assert rel_l2(got[s][:, 40:], want[s][:, 40:]) <= 1e-6
