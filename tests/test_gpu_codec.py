@@ -160,10 +160,10 @@ def test_encode_decode_parity(name, tensor, T, ratio):
 
 @pytest.mark.parametrize("ratio", [12.0, 8.0, 4.0, 3.0, 16.0 / 9.0])
 def test_decode_many_super_tiles_per_workgroup(ratio):
-    """Mode A decode of 32 streams over a window whose first and last 128-token
-    super-tiles are partial: the decode grid gives each stream 16 workgroups, so some
-    walk two super-tiles (records of up to 32 words double-buffered in LDS, wider ones
-    through one buffer). P6 on identical bytes against the oracle for every stream."""
+    """Mode A decode of 32 streams over a window whose first and last 64-token tiles are
+    partial, at record widths from 5 to 36 words: 39 tiles per stream, one per wavefront (more per
+    wavefront: test_decode_several_tiles_per_wavefront). P6 on identical bytes against the
+    oracle for every stream."""
     w = synth.WORKLOADS["llama_batch16_12x"]
     T, t0, n = 2500, 37, 2400
     x = _streams(w, 0, T, n_streams=32)

@@ -9,7 +9,7 @@ import pytest
 
 import paper_2608_07915_amd as S
 from gpu_parity import rel_l2
-from layer_records import make_layer_cache
+from layer_records import make_layer_cache, repeat_streams
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +51,23 @@ def test_layer_decode_weak_channels(split, weak):
     for s in range(2):
         assert rel_l2(got[s][:, 5:40], want[s][:, 5:40] * weak) <= 1e-6
         assert rel_l2(got[s][:, 40:], want[s][:, 40:]) <= 1e-6
+
+
+LONG = [
+    # d, widths, tokens, first slot, streams, times over, square-root split
+    (256, [5, 3, 0, 8], 256 * 5 + 70, 17, 4, 32, True),             # one workgroup per block: six ranges each
+    (384, [4, 0, 3, 1, 7, 2], 256 * 9 - 1, 0, 2, 14, True),         # three per block: three ranges each
+    (1024, [2] * 12 + [0] * 4, 256 * 7 + 1, 64, 1, 8, False),       # four per block: two ranges each
+]
+
+
+@pytest.mark.parametrize("d,widths,T,t0,n,times,split", LONG)
+def test_layer_decode_several_ranges(d, widths, T, t0, n, times, split):
+    """So many streams that a workgroup walks several ranges with the same staged blocks."""
+    rng = np.random.default_rng([d, T, t0])
+    codec, packed, t_cap, want = make_layer_cache(rng, d, widths, T, t0, n, split=split)
+    codec, packed = repeat_streams(codec, packed, times)
+    got = S.spectra_decode(codec, packed, t_cap, t0, T)
+    for s in range(n):
+        assert rel_l2(got[s].cpu().numpy(), want[s]) <= 1e-6
+        assert torch.equal(got[s::n], got[s].expand(times, T, d))
