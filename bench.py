@@ -42,20 +42,20 @@ CALIB_BYTES = 256 << 20
 # 262148 KiB for 256 MiB written: x1.0). Valid only for the kernel sources they
 # were taken on (sha256 over DECODE_STEP_SOURCES); otherwise `traffic` is null.
 DECODE_STEP_SOURCES = ("kernels_attn.hip", "attn_common.hpp", "kplan.hpp", "encode_dev.hpp", "device_common.hpp",
-                       "kernels.hpp")
+                       "kernels.hpp", "splits.hpp")
 # sha256 -> fetch / write bytes per call; per_kernel: [fetch, write]
 MEASURED_TRAFFIC = {
-    "0dc6e80a2b7f61b0b562fde7cbff11884cbad20ea2f1c2a005395111734033e8": {
-        "fetch_bytes": 74542716, "write_bytes": 1674244, "mfma_busy": 0.096,
-        "per_kernel": {"attn_kernel<1,8,8,true>": [70734430, 1657860], "combine_kernel": [3808286, 16384]}},
+    "0a86f480dbdd0e2986c2289ca217db35a8e12f1034acc37a464cb5d90e1c86c3": {
+        "fetch_bytes": 74539970, "write_bytes": 1674243, "mfma_busy": 0.096,
+        "per_kernel": {"attn_kernel<1,8,8,true>": [70698946, 1657859], "combine_kernel": [3841024, 16384]}},
 }
 # The same passes over the bulk encode of one codec (256 streams x 131072 tokens):
 # HBM bytes per call and the matrix cores' busy fraction (SQ_VALU_MFMA_BUSY_CYCLES
 # over GRBM_GUI_ACTIVE x 1024 SIMDs), keyed by sha256 over ENCODE_SOURCES.
 ENCODE_SOURCES = ("kernels_codec.hip", "encode_dev.hpp", "device_common.hpp", "kernels.hpp")
 MEASURED_ENCODE = {
-    "39359687aa625a2fad9927ac1b89124751d52288a590f4d285f932dbf9896b21": {
-        "fetch_bytes": 8665222080, "write_bytes": 1073741824, "mfma_busy": 0.368},
+    "fea7321d3eb175cd29a6382afcb82e456eba52b482c9b6dc0850e4904a3e904a": {
+        "fetch_bytes": 8665611008, "write_bytes": 1073741824, "mfma_busy": 0.365},
 }
 
 

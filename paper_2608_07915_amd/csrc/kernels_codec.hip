@@ -360,7 +360,8 @@ __global__ __launch_bounds__(256, 2) void encode_f32_kernel(EncodeArgs a) {
 // Bound by the fp32 rows written: 537 MB for eight heads of 131k tokens, 106 us for stores
 // alone in this pattern. With 32 channels per wavefront, three bf16 parts and every code
 // unpacked by four wavefronts 176 us, now 128 us at 8x. Whole tiles take all 256 registers and
-// spill 20 (44 bytes of scratch per lane), half tiles take 194.
+// spill 22 (48 bytes of scratch a lane; the counters see no more written to HBM than the rows,
+// and the vector ALU busy 16% of the time), half tiles take 195.
 constexpr int DC_NW = HB_NW;  // wavefronts per workgroup
 static_assert(DC_NW == spectra::DECODE_WAVES, "wavefronts of a workgroup");
 __host__ __device__ constexpr int decode_lds_bytes() { return hb_lds_bytes(); }

@@ -340,11 +340,12 @@ __global__ __launch_bounds__(512, 4) void layer_encode_kernel(LayerEncodeArgs a)
 // each side), and m V^T is added last.
 // The codes are the row operand and column c of channel block b is channel 4c + b, so every
 // store of a wavefront is two whole 512-byte row pieces.
-// A 131k-token 1024-wide layer at 8x: 1860 -> 483 us. Matrix cores busy 45%, vector ALU
-// 44%, the rest is the store bursts at a range's end and waiting inside a step. What was tried and is slower: a workgroup per range (720 us:
-// its prologue and epilogue overlap nothing), 64 tokens x 64 channels per wavefront (560
-// us, every code unpacked twice), 64 x 128 (490 to 520 us, spills), four wavefronts
-// with four times the registers (770 us).
+// A 131k-token 1024-wide layer at 8x: 1860 -> 481 us. The counters have the matrix cores busy
+// 43% of the time and the vector ALU 42%; the wavefronts wait 29% of their cycles (the store
+// bursts at a range's end, LDS inside a step) and 33% for their turn to issue. What was tried
+// and is slower: a workgroup per range (720 us: its prologue and epilogue overlap nothing), 64
+// tokens x 64 channels per wavefront (560 us, every code unpacked twice), 64 x 128 (490 to 520
+// us, spills), four wavefronts with four times the registers (770 us).
 constexpr int LD_CH = 128;     // channels per workgroup
 constexpr int LD_NW = 8;       // wavefronts per workgroup
 constexpr int LD_TOK = 32 * LD_NW;  // tokens per range

@@ -251,8 +251,10 @@ __global__ __launch_bounds__(64 * LA_SW, 4) void layer_scores_kernel(LayerAttnAr
 // Values: one workgroup per (two score chunks, block of 16 query heads, half of the kept
 // slots, sequence); wavefront w takes kept value slot w or w + 8. The halves are workgroups
 // of their own so that two fit a CU (four wavefronts per SIMD): with both slots in one
-// wavefront 61 us for a 131k-token 1024-wide layer at 8x, now 58 us (codes taken one
-// at a time from staged rows, both slots: 91 us).
+// wavefront 61 us for a 131072-token 1024-wide layer at 8x, now 58 us (codes taken one
+// at a time from staged rows, both slots: 91 us). At 131104 tokens the chunks are 18 tiles
+// instead of 16 on 456 workgroups instead of 512: 67 us. The form for more than 64 words
+// spills 15 registers (60 bytes of scratch a lane).
 // ---------------------------------------------------------------------------
 // Lane (kg, c16) of a product over 32 tokens supplies coefficients 4 c16 .. 4 c16 + 3 of
 // the group for tokens 8 kg .. 8 kg + 7: four codes are at most 32 adjacent bits, so one

@@ -944,9 +944,11 @@ __global__ __launch_bounds__(R4T, 2) void rope_attn4_kernel(AttnArgs a) {
 // With four wavefronts sharing a tile (each 32 dimensions, codes and partial scores through
 // LDS, two barriers per tile, the softmax in all four, three bf16 parts) a Llama layer call
 // over 131k tokens at 8x took 183 us, now 119 us (4x records 224 -> 152 us; 12x 151 -> 100;
-// seven heads, 65k tokens 77 -> 68; 1000 tokens 37 -> 29). The card's counters name no single
-// bound: about half the time the vector units issue (unpack, rotation), the rest the one
-// chain per SIMD pair waits.
+// seven heads, 65k tokens 76 -> 65, but 72 -> 71 over keys of one group at 7 bits; 1000 tokens
+// 37 -> 29). The card's counters name no single bound: 52% of the time the vector units issue
+// (unpack, rotation), the matrix cores are busy 16%, and the two wavefronts of a SIMD wait 43%
+// of their cycles. All forms take 256 registers; eight heads spill 45 more (120 bytes of
+// scratch a lane), 16 words 6.
 // ---------------------------------------------------------------------------
 constexpr int RW_NW = HB_NW;
 static_assert(RW_NW == spectra::ROPE_WAVE_TILES, "a tile per wavefront");
