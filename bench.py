@@ -45,7 +45,7 @@ DECODE_STEP_SOURCES = ("kernels_attn.hip", "attn_common.hpp", "kplan.hpp", "enco
                        "kernels.hpp", "splits.hpp")
 # sha256 -> fetch / write bytes per call; per_kernel: [fetch, write]
 MEASURED_TRAFFIC = {
-    "0a86f480dbdd0e2986c2289ca217db35a8e12f1034acc37a464cb5d90e1c86c3": {
+    "1dabd5c89f623b1f30fca90c9d9e08e714d9e2ba24a4c1cc441ba19cea1e5927": {
         "fetch_bytes": 74539970, "write_bytes": 1674243, "mfma_busy": 0.096,
         "per_kernel": {"attn_kernel<1,8,8,true>": [70698946, 1657859], "combine_kernel": [3841024, 16384]}},
 }
@@ -54,7 +54,7 @@ MEASURED_TRAFFIC = {
 # over GRBM_GUI_ACTIVE x 1024 SIMDs), keyed by sha256 over ENCODE_SOURCES.
 ENCODE_SOURCES = ("kernels_codec.hip", "encode_dev.hpp", "device_common.hpp", "kernels.hpp")
 MEASURED_ENCODE = {
-    "fea7321d3eb175cd29a6382afcb82e456eba52b482c9b6dc0850e4904a3e904a": {
+    "fb9a14b725b1e723ac5aafd8bb3ba212132534c397aa05c524a94e674f215aea": {
         "fetch_bytes": 8665611008, "write_bytes": 1073741824, "mfma_busy": 0.365},
 }
 

@@ -469,7 +469,6 @@ static spectra_status prepare_attention(const char* name, const spectra_codec* c
   const float sc = softmax_scale > 0.0f ? softmax_scale : 1.0f / std::sqrt((float)kD);
   a.scale_log2 = sc * 1.4426950408889634f;
   a.partial = reinterpret_cast<float*>(workspace);
-  a.max_chunks = (int32_t)std::min(ws_bytes / (attention_partial_floats(batch, n_q_heads, 1) * sizeof(float)), (size_t)1 << 30);
   a.out = out;
   *args = a;
   return SPECTRA_OK;

@@ -79,7 +79,6 @@ struct AttnArgs {
   int64_t t_new;
   int32_t app_f32;
   float* partial;        // workspace: per-chunk softmax partials
-  int32_t max_chunks;    // that it has room for, per (batch, kv head)
   float* out;            // [batch][n_q_heads][128]
   // attention with rotary position embeddings only: pair frequencies [64] (device)
   // and the query's position (key t sits at position t)

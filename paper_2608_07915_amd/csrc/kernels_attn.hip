@@ -799,17 +799,17 @@ static int32_t launch_nq_pw(const AttnArgs& a, hipStream_t st) {
   size_t merge = (size_t)WAVES * (NQ <= 2 ? 8 * NQ : 4 * NQ) * AROW * 4;  // per-wave value sums
   size_t lds = tiles > merge ? tiles : merge;
   if ((size_t)qprep_scratch_bytes(NQ) > lds) lds = qprep_scratch_bytes(NQ);
-  if (a.app_k && (size_t)append_stage_bytes(a.app_f32 != 0) > lds) lds = append_stage_bytes(a.app_f32 != 0);
   // more (sequence, kv head) groups than XCDs: chunks of a group kept on one XCD
   AttnArgs g = a;
   const int64_t groups = (int64_t)a.n_kv_heads * a.batch;
   g.group_major = groups > 8 ? 1 : 0;
   // workgroups a CU holds: three wavefronts per SIMD by the registers of the shapes with one
   // head quad and at most 24 prefetched words, two for the others; and its 160 KB of LDS
+  // (that of a call without an append: a decode step has the same split)
   constexpr int REGS = NQ == 1 && PK + PV <= 24 ? 3 : 2;
   const int fit = (int)(160 * 1024 / (lds + attn_static_lds(NQ)));
-  const Split split = scan_split(groups, (a.n_tokens + 63) / 64, fit < 1 ? 1 : fit < REGS ? fit : REGS, NQ * (a.Wk + a.Wv),
-                                 a.app_k != nullptr, a.max_chunks);
+  if (a.app_k && (size_t)append_stage_bytes(a.app_f32 != 0) > lds) lds = append_stage_bytes(a.app_f32 != 0);
+  const Split split = scan_split(groups, (a.n_tokens + 63) / 64, fit < 1 ? 1 : fit < REGS ? fit : REGS, NQ * (a.Wk + a.Wv));
   g.tiles_per_chunk = split.tiles_per_chunk;
   g.n_chunks = split.n_chunks;
   const dim3 grid = g.group_major ? dim3(g.n_chunks * a.n_kv_heads * a.batch, 1, 1) : dim3(g.n_chunks, a.n_kv_heads, a.batch);

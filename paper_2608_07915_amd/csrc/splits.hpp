@@ -68,10 +68,6 @@ inline int32_t attention_workspace_chunks(int64_t groups, int64_t n_tiles) {
   const int64_t body = ceil_div(n_tiles - 1, 16), rope = ceil_div(n_tiles, 4);
   int64_t n = (body < want ? body : want) + 1;
   if (n < rope && n < rope_want) n = rope < rope_want ? rope : rope_want;
-  if (groups <= 8) {  // the scan takes chunks of eight tiles where there is room
-    const int64_t eight = ceil_div(n_tiles - 1, 8) + 1, most = 768 / groups;
-    if (n < eight && n < most) n = eight < most ? eight : most;
-  }
   return (int32_t)n;
 }
 
@@ -79,62 +75,51 @@ inline int32_t attention_workspace_chunks(int64_t groups, int64_t n_tiles) {
 // Latent attention scan
 // ---------------------------------------------------------------------------
 // Split for a scan kernel of which a CU holds per_cu workgroups of four wavefronts, a tile per
-// wavefront and step, in a workspace with room for `room` chunks (at least
-// attention_max_chunks). The last tile is a chunk of its own (in a decode step its workgroup
-// also appends the new token); the others come in chunks of at least 8 tiles.
-//
-// As many chunks as fill the slots: a few workgroups beyond the slots start when the others
-// end and nearly double the scan's time (32k tokens at 4x, 512 slots: 520 workgroups 33.5 us,
-// 352 workgroups 26.5), so the count is rounded down, over the fewest rounds of workgroups
-// that come out 85% full. The last tiles' workgroups need slots too. Up to eight groups the
-// other chunks make room. Above, they are the last of the grid and may queue, which costs
-// about a 32nd of a tile per group where three fit a CU (32 groups, 33000 tokens at 8x: chunks
-// of 24 tiles 42.4 us, of 22 and a queue 43.8; 64 groups, 30000 tokens: 63.7 and 59.9); two
-// per CU hold the line at four steps per chunk and group. A queue of less than half of them
-// behind last chunks that end early costs least, and saves the step that longer chunks would
-// add (40 groups, 12000 tokens at 4x: 37.1 and 40.2).
-// Calls against chunks of at least 16 tiles for 768 workgroups: 32k tokens at 4x 35.5 -> 31.0
-// us, seven heads over 65k tokens 38.0 -> 34.2, 1000 tokens 21.9 -> 17.6; equal from 48k to
-// 131k tokens at 8x.
+// wavefront and step. The last tile is a chunk of its own (in a decode step its workgroup also
+// appends the new token); the others come in chunks of at least 8 tiles. The cuts set the order
+// of the sums, and a decode step returns what attention alone does over the same records, so
+// they depend on nothing that differs between the two calls.
 //
 // In a decode step the append is the longest chain of a short cache, and more workgroups only
 // take its CU's time: there the shortest chunks of 8, 12 or 16 tiles that leave every
 // workgroup a CU of its own (eight heads at 12x, 20000 tokens: 23.3 us by 320 workgroups, 21.1
-// by 216; at 8x 24.3 and 22.5). The heavier a tile, the less that counts. `weight` is the head
-// quads times the words of both records: above 24 (four heads at 4x, seven at 8x) chunks of 16
-// lose against more workgroups (two sequences of 12000 tokens at 4x 30.1 and 29.1 us), above
-// 32 (seven heads at 4x) so do all (32768 tokens 36.8 and 35.6).
+// by 216; at 8x 24.3 and 22.5). Attention alone would rather have more of them (eight heads at
+// 8x, 28000 tokens: 21.0 us by 440 workgroups, 23.1 by 232, which take 25.3 and 23.5 for the
+// step; 128 groups of 1000 tokens 25.8 and 30.1, the step 42.4 and 40.3). The heavier a tile,
+// the less the append counts. `weight` is the head quads times the words of both records: above
+// 24 (four heads at 4x, seven at 8x) chunks of 16 lose against more workgroups (two sequences of
+// 12000 tokens at 4x 30.1 and 29.1 us), above 32 (seven heads at 4x) so do all (32768 tokens
+// 36.8 and 35.6).
+//
+// Otherwise as many chunks as fill the slots: a few workgroups beyond the slots start when the
+// others end and nearly double the scan's time (32k tokens at 4x, 512 slots: 520 workgroups
+// 33.5 us, 352 workgroups 26.5), so the count is rounded down, over the fewest rounds of
+// workgroups that come out 85% full. The last tiles' workgroups need slots too. Up to eight
+// groups the other chunks make room. Above, they are the last of the grid, and queue when the
+// slot that one takes would cost the other chunks a tile per wavefront (64 groups at 8x, 16000
+// tokens: the step 54.6 us with a queue, 45.1 without; 30000: 66.8 and 65.0, attention alone
+// 59.3 and 63.2).
+// Calls against chunks of at least 16 tiles for 768 workgroups: 32k tokens at 4x 35.5 -> 31.0
+// us, seven heads over 65k tokens 38.0 -> 34.2, 1000 tokens 21.9 -> 17.6; equal from 48k to
+// 131k tokens at 8x.
 constexpr int SCAN_WAVES = 4;
-inline Split scan_split(int64_t groups, int64_t n_tiles, int per_cu, int weight, bool append, int64_t room) {
+inline Split scan_split(int64_t groups, int64_t n_tiles, int per_cu, int weight) {
   const int64_t body = n_tiles - 1, slots = N_CU * per_cu;
   if (body < 1) return Split{1, 1};
-  auto steps = [](int64_t tiles) { return ceil_div(tiles, SCAN_WAVES); };
-  if (append)
-    for (int64_t t = 8; t <= (weight <= 24 ? 16 : weight <= 32 ? 12 : 0); t += SCAN_WAVES)
-      if (groups * (ceil_div(body, t) + 1) <= N_CU) return Split{(int32_t)t, (int32_t)ceil_div(body, t) + 1};
-  int64_t n = 0, held = 0;
+  for (int64_t t = 8; t <= (weight <= 24 ? 16 : weight <= 32 ? 12 : 0); t += SCAN_WAVES)
+    if (groups * (ceil_div(body, t) + 1) <= N_CU) return Split{(int32_t)t, (int32_t)ceil_div(body, t) + 1};
+  int64_t n = 0;
   for (int64_t rounds = 1; rounds <= 4; ++rounds) {
-    held = rounds * slots;
-    n = held / groups;
-    if (n * groups * 100 >= 85 * held) break;
+    n = rounds * slots / groups;
+    if (n * groups * 100 >= 85 * rounds * slots) break;
   }
-  if (n > 1) {
-    const int64_t t = steps(ceil_div(body, n)) * SCAN_WAVES, last = body - (ceil_div(body, t) - 1) * t;
-    const bool short_queue = t >= 16 && steps(ceil_div(body, n - 1)) * SCAN_WAVES > t && steps(last) * SCAN_WAVES < t &&
-                             2 * (groups * (n + 1) - held) < groups;
-    if (groups > 8 && !append && short_queue)
-      n = ceil_div(body, t);
-    else if (groups <= 8 || (per_cu == 3 && !append ? 32 * ceil_div(body, n) < (n - 1) * groups : body < SCAN_WAVES * n * n))
-      --n;
-  }
-  // longer chunks for want of room only where the workspace has none (an append is better off
-  // with them: 32000 tokens of eight heads at 4x 31.4 us by chunks of 12, 34.2 by 8)
-  const int64_t cap = (groups <= 8 && !append ? room : attention_max_chunks(groups, n_tiles)) - 1, most = ceil_div(body, 8);
+  if (n > 1 && (groups <= 8 || body < SCAN_WAVES * n * n)) --n;
+  const int64_t cap = attention_max_chunks(groups, n_tiles) - 1, most = ceil_div(body, 8);
   if (n > cap) n = cap;
   if (n > most) n = most;
   if (n < 1) n = 1;
   int64_t tpc = ceil_div(body, n);
-  if (tpc < 16) tpc = steps(tpc) * SCAN_WAVES;  // whole steps
+  if (tpc < 16) tpc = ceil_div(tpc, SCAN_WAVES) * SCAN_WAVES;  // whole steps
   return Split{(int32_t)tpc, (int32_t)ceil_div(body, tpc) + 1};
 }
 

@@ -62,25 +62,21 @@ int main() {
       CHECK(cap <= ws && ws >= most, "%lld groups, %lld tiles: %d, %d, %d", (long long)g, (long long)tiles, cap, ws, most);
       most = ws;
       for (int per_cu : {1, 2, 3})
-        for (int weight : {10, 24, 25, 32, 33, 64})
-          for (int32_t room : {cap, ws, 1 << 20}) {
-            for (bool append : {false, true}) {
-              // the last tile is a chunk of its own
-              const Split c = scan_split(g, tiles, per_cu, weight, append, room);
-              if (tiles > 1)
-                covers("scan", g, tiles - 1, Split{c.tiles_per_chunk, c.n_chunks - 1});
-              else
-                CHECK(c.n_chunks == 1, "scan: %d chunks of one tile", c.n_chunks);
-              CHECK(c.n_chunks <= room, "scan: %lld groups, %lld tiles: %d chunks, room for %d", (long long)g, (long long)tiles, c.n_chunks, room);
-              // a light shape's append shares its CU with no other workgroup where chunks of 16
-              // tiles can do that
-              CHECK(!append || weight > 24 || g * (ceil_div(tiles - 1, 16) + 1) > 256 || g * c.n_chunks <= 256,
-                    "step: %lld groups, %lld tiles: %d chunks", (long long)g, (long long)tiles, c.n_chunks);
-              // up to eight groups: the last tiles' workgroups are held with the others
-              CHECK(g > 8 || g * c.n_chunks <= 256 * per_cu, "scan: %lld groups, %lld tiles: %d chunks of %d", (long long)g, (long long)tiles,
-                    c.n_chunks, c.tiles_per_chunk);
-            }
-          }
+        for (int weight : {10, 24, 25, 32, 33, 64}) {
+          // the last tile is a chunk of its own
+          const Split c = scan_split(g, tiles, per_cu, weight);
+          if (tiles > 1)
+            covers("scan", g, tiles - 1, Split{c.tiles_per_chunk, c.n_chunks - 1});
+          else
+            CHECK(c.n_chunks == 1, "scan: %d chunks of one tile", c.n_chunks);
+          CHECK(c.n_chunks <= cap, "scan: %lld groups, %lld tiles: %d chunks, room for %d", (long long)g, (long long)tiles, c.n_chunks, cap);
+          // a light shape's workgroups have a CU each where chunks of 16 tiles can do that
+          CHECK(weight > 24 || g * (ceil_div(tiles - 1, 16) + 1) > 256 || g * c.n_chunks <= 256,
+                "scan: %lld groups, %lld tiles: %d chunks", (long long)g, (long long)tiles, c.n_chunks);
+          // up to eight groups: the last tiles' workgroups are held with the others
+          CHECK(g > 8 || g * c.n_chunks <= 256 * per_cu, "scan: %lld groups, %lld tiles: %d chunks of %d", (long long)g, (long long)tiles,
+                c.n_chunks, c.tiles_per_chunk);
+        }
       for (int n_qh = 1; n_qh <= 8; n_qh += 3)
         for (int words : {4, 8, 9, 16, 17, 32}) {
           const RopeSplit r = rope_split(g, n_qh, words, tiles);

@@ -10,6 +10,7 @@ import oracle as O
 import paper_2608_07915_amd as S
 import synth
 from gpu_parity import fit_and_encode, to_device
+from layer_records import make_layer_cache, repeat_streams
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +60,39 @@ def test_decode_step_equals_encode_then_attention(name, T0, batch, ratio, kappa)
         assert torch.equal(pv, pv2), (name, t)
         assert torch.equal(got, want), (name, t)
         assert got.shape == (batch, Hq, 128)
+
+
+@pytest.mark.parametrize("T0,batch,kv,nqh,widths", [
+    # where the append, the workspace or a queue could move the cuts between workgroups
+    (19999, 1, 8, 4, ([4, 2, 0, 0], [3, 1, 1, 0])),
+    (30000, 1, 8, 4, ([2, 1, 0, 0], [2, 0, 0, 1])),
+    (29999, 1, 8, 4, ([5, 3, 2, 2], [2, 3, 4, 3])),
+    (33000, 1, 4, 7, ([4, 2, 0, 0], [3, 1, 1, 0])),
+    (11999, 5, 8, 4, ([5, 3, 2, 2], [2, 3, 4, 3])),
+    (4000, 5, 8, 4, ([4, 2, 0, 0], [3, 1, 1, 0])),
+    (999, 16, 8, 4, ([4, 2, 0, 0], [3, 1, 1, 0])),
+])
+def test_decode_step_long_caches(T0, batch, kv, nqh, widths):
+    """The same over caches of many chunks, with the smallest workspace and a larger one: the sums
+    are split alike, so the outputs are identical."""
+    rng = np.random.default_rng([T0, batch, kv])
+    n, t_cap = batch * kv, (T0 + 64) // 64 * 64
+    g = torch.Generator(device="cuda").manual_seed(T0)
+    caches = []
+    for w in widths:
+        codec, packed, _, _ = make_layer_cache(rng, 128, w, 64, 0, 4, g=32)
+        codec, _ = repeat_streams(codec, packed, n // 4)
+        x = torch.randn((n, T0 + 1, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+        rec = codec.empty_packed(t_cap)
+        S.spectra_encode(codec, x[:, :T0].contiguous(), 0, rec, t_cap)
+        caches.append((codec, rec, x[:, T0].reshape(batch, kv, 128).contiguous()))
+    (ck, pk, k_new), (cv, pv, v_new) = caches
+    q = 0.3 * torch.randn((batch, kv * nqh, 128), generator=g, device="cuda")
+    need = S.spectra_attention_workspace_bytes(batch, kv * nqh, kv, T0 + 1)
+    got = [S.spectra_decode_step(ck, cv, pk, pv, t_cap, T0, k_new, v_new, q, kv,
+                                 workspace=torch.empty(r * need, dtype=torch.uint8, device="cuda")) for r in (1, 4)]
+    want = [S.spectra_decode_attention(ck, cv, pk, pv, t_cap, T0 + 1, q, kv,
+                                       workspace=torch.empty(r * need, dtype=torch.uint8, device="cuda")) for r in (1, 4)]
+    assert torch.isfinite(want[0]).all()
+    for o in got + want[1:]:
+        assert torch.equal(o, want[0]), (T0, batch)

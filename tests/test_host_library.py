@@ -235,16 +235,14 @@ def test_layer_geometry_argument_errors(lib):
 @pytest.mark.parametrize("batch,kv", [(1, 1), (1, 4), (1, 8), (2, 4), (3, 8), (5, 4), (16, 8), (97, 8), (300, 3)])
 def test_attention_workspace_never_shrinks(lib, batch, kv):
     """A workspace taken for a longer cache serves every shorter one: its size never falls with
-    the token count, and is the largest number of chunks that any of them may need (chunks of 16
-    or more tiles for 768 workgroups, or with up to eight groups of eight for no more of them,
-    and the last tile; of four or more for 512)."""
+    the token count, and is the largest number of chunks that any of them is split into (chunks
+    of 16 or more tiles for 768 workgroups and the last tile; of four or more for 512)."""
     def own(tiles):
         g = batch * kv
         want, rope_want = -(-768 // g), -(-512 // g)
         body = tiles - 1
         scan = -(-body // max(16, -(-body // want))) + 1
-        eight = min(-(-body // 8) + 1, 768 // g) if g <= 8 else 0
-        return max(scan, eight, -(-tiles // max(4, -(-tiles // rope_want))))
+        return max(scan, -(-tiles // max(4, -(-tiles // rope_want))))
     most = 0
     for tiles in list(range(1, 700)) + list(range(700, 6000, 13)):
         most = max([most] + [own(t) for t in (range(tiles - 12, tiles + 1) if tiles > 700 else [tiles])])
